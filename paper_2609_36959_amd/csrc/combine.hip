@@ -18,8 +18,8 @@
 // single store so that no load waits behind a store.
 //
 // The node-level combine (the reverse of the node-deduplicated dispatch)
-// follows: node_fold_kernel sums each node's slots into a bf16 partial row,
-// node_sum_kernel sums a token's partial rows in node order.
+// follows: node_fold_kernel sums each node's slots into a bf16 partial row
+// and the token's partial rows, in node order, into y.
 #include <algorithm>
 
 #include "internal.hpp"
@@ -28,8 +28,7 @@ namespace cobalt {
 namespace {
 
 constexpr int kCombineWaves = 16;
-constexpr int kFoldWaves = 2;  // waves that fold or sum a staged slice (128 chunks, one per thread)
-constexpr int kNodeWaves = 4;  // least waves of node_fold_kernel; waves of node_sum_kernel
+constexpr int kFoldWaves = 2;  // waves that fold a staged slice (128 chunks, one per thread)
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -190,22 +189,28 @@ bool try_fold(const void* eo, const int32_t* pos, const float* gates, int64_t T,
     }
 }
 
-// Node side of the node-level combine: one workgroup per (token, 2 KiB
-// column slice), one wave per slot j (at least four waves). Wave j loads its
-// row's slice like fold_kernel and records its gate and its rank's node;
-// after a barrier each wave folds whole node rows: for each node the token
-// reaches, the slots on that node in slot order, stored as the bf16 partial
-// in the token's row for that node. GROUPS as for fold_kernel.
+// Node-level combine: one workgroup per (token, 2 KiB column slice), one wave
+// per slot j (at least two waves). Wave j loads its row's slice like
+// fold_kernel and records its gate and its rank's node; after a barrier two
+// waves, one 16-byte chunk per thread, go through the token's node rows in
+// node order: each is the sum of the node's slots in slot order, rounded to
+// bf16, stored as the partial row's slice and added to y. The partials
+// stay in registers on their way into y: with a second kernel that read the
+// node rows back the call moved a third more bytes and took 5.6 ms on the
+// T=131072, K=8, N=8, d=7168 workload (3.93 + 1.67), now 4.35 ms (5.8 TB/s of
+// mixed reads and writes). One wave per node row, with the partials summed
+// through LDS after a second barrier, took 4.46 ms; plain instead of
+// non-temporal stores of the partial rows 4.42 ms.
+// GROUPS as for fold_kernel.
 template <int GROUPS>
 __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
     const u32x4* __restrict__ eo, const int32_t* __restrict__ pos,
     const int32_t* __restrict__ assigned, const float* __restrict__ gates,
     const int32_t* __restrict__ node_pos, int K, int N, int gpn, int64_t nch, int64_t TK,
-    int64_t node_rows, int groups_rt, u32x4* __restrict__ partial) {
+    int64_t node_rows, int groups_rt, u32x4* __restrict__ partial, u32x4* __restrict__ y) {
     extern __shared__ u32x4 stage[];
     __shared__ float gate[kMaxK];
     __shared__ int slot_node[kMaxK];  // node of slot j's rank, -1 for a skipped slot
-    __shared__ int nrow[kMaxN];       // row of (t, n) in partial, -1 if none
     const uint32_t groups = GROUPS ? GROUPS : (uint32_t)groups_rt;
     const uint32_t tg = blockIdx.x;
     const uint32_t t = tg / groups;
@@ -230,165 +235,69 @@ __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
             slot_node[j] = ok ? r / gpn : -1;
         }
     }
-    if (j == 0 && lane < N) {
+    // lane n of the folding waves holds the row of (t, n) in partial
+    int row = -1;
+    if (j < kFoldWaves && lane < N) {
         const int q = node_pos[(int64_t)t * N + lane];
-        nrow[lane] = q >= 0 && q < node_rows ? q : -1;
+        row = q >= 0 && q < node_rows ? q : -1;
     }
     __syncthreads();
-    // Wave w folds the rows of nodes w, w + waves, ...: for each, it sums the
-    // node's slots in slot order over its two chunks per lane and stores the
-    // row's 2 KiB slice itself (splitting a row over four waves, eight bytes
-    // per lane, took 3 % longer).
-    const int waves = blockDim.x >> 6;
-    for (int n = j; n < N; n += waves) {
-        const int q = nrow[n];
-        if (q < 0) continue;
-        float acc[2][8];
+    if (j >= kFoldWaves) return;
+    const int i = threadIdx.x;
+    const int64_t c = (int64_t)g * 128 + i;
+    const int node = lane < K ? slot_node[lane] : -1;  // lane k holds slot k's node and gate
+    const int gk = lane < K ? __float_as_int(gate[lane]) : 0;
+    float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (uint64_t nodes = __ballot(row >= 0); nodes; nodes &= nodes - 1) {
+        const int n = __builtin_ctzll(nodes);
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (uint64_t slots = __ballot(node == n); slots; slots &= slots - 1) {
+            const int k = __builtin_ctzll(slots);
+            const float gv = __int_as_float(__builtin_amdgcn_readlane(gk, k));
+            const u32x4 v = stage[k * 128 + i];
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
-        for (int k = 0; k < K; ++k) {
-            if (slot_node[k] != n) continue;
-            const float gk = gate[k];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const u32x4 v = stage[k * 128 + lane + 64 * h];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[h][2 * e] = __builtin_fmaf(gk, __uint_as_float(v[e] << 16), acc[h][2 * e]);
-                    acc[h][2 * e + 1] =
-                        __builtin_fmaf(gk, __uint_as_float(v[e] & 0xffff0000u), acc[h][2 * e + 1]);
-                }
+            for (int e = 0; e < 4; ++e) {
+                acc[2 * e] = __builtin_fmaf(gv, __uint_as_float(v[e] << 16), acc[2 * e]);
+                acc[2 * e + 1] =
+                    __builtin_fmaf(gv, __uint_as_float(v[e] & 0xffff0000u), acc[2 * e + 1]);
             }
         }
-        u32x4* dst = partial + (int64_t)q * nch;
+        u32x4 part;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (!(h == 0 ? in0 : in1)) continue;
-            u32x4 out;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                out[e] = pack_bf16_rne(acc[h][2 * e], acc[h][2 * e + 1]);
-            __builtin_nontemporal_store(out, dst + c0 + 64 * h);
+        for (int e = 0; e < 4; ++e) {
+            part[e] = pack_bf16_rne(acc[2 * e], acc[2 * e + 1]);
+            sum[2 * e] += __uint_as_float(part[e] << 16);
+            sum[2 * e + 1] += __uint_as_float(part[e] & 0xffff0000u);
         }
+        const int q = __builtin_amdgcn_readlane(row, n);
+        if (c < nch) __builtin_nontemporal_store(part, partial + (int64_t)q * nch + c);
     }
+    if (c >= nch) return;
+    u32x4 out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        out[e] = pack_bf16_rne(sum[2 * e], sum[2 * e + 1]);
+    __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
 }
 
 template <int GROUPS>
 void launch_node_fold(const void* eo, const int32_t* pos, const int32_t* assigned,
                       const float* gates, const int32_t* node_pos, int64_t T, int K, int N,
-                      int gpn, int64_t nch, int64_t node_rows, void* partial, hipStream_t s) {
+                      int gpn, int64_t nch, int64_t node_rows, void* partial, void* y,
+                      hipStream_t s) {
     const int64_t groups = (nch + 127) / 128;
     if constexpr (GROUPS > 0) {
         if (groups != GROUPS)
             return launch_node_fold<GROUPS - 1>(eo, pos, assigned, gates, node_pos, T, K, N, gpn,
-                                                nch, node_rows, partial, s);
+                                                nch, node_rows, partial, y, s);
     }
-    const int threads = std::max(K, kNodeWaves) * 64;
+    const int threads = std::max(K, kFoldWaves) * 64;
     for_token_ranges(T, groups * threads, [&](int64_t t0, int64_t n) {
         hipLaunchKernelGGL(node_fold_kernel<GROUPS>, dim3((unsigned)(n * groups)), dim3(threads),
                            (size_t)K * 128 * sizeof(u32x4), s, (const u32x4*)eo, pos + t0 * K,
                            assigned + t0 * K, gates + t0 * K, node_pos + t0 * N, K, N, gpn, nch,
-                           T * K, node_rows, (int)groups, (u32x4*)partial);
-    });
-}
-
-// Source side of the node-level combine: one workgroup of four waves per
-// (token, 2 KiB column slice). Wave j loads the node rows n = j, j + 4, ...
-// (SPW of them at most) that node_pos names for the token; after a barrier
-// two waves sum the staged rows in increasing n, one 16-byte chunk per
-// thread, and store the slice of y (four waves at 8 bytes per thread were
-// no faster). A token reaches only about
-// half of the nodes, so one loading wave per node would leave half the
-// waves idle at the barrier (1.91 ms against 1.65 ms on the T=131072, N=8,
-// d=7168 workload).
-// GROUPS as for node_fold_kernel.
-template <int GROUPS, int SPW>
-__global__ __launch_bounds__(kNodeWaves * 64) void node_sum_kernel(
-    const u32x4* __restrict__ partial, const int32_t* __restrict__ node_pos, int N, int64_t nch,
-    int64_t node_rows, int groups_rt, u32x4* __restrict__ y) {
-    extern __shared__ u32x4 stage[];
-    __shared__ int valid[kMaxN];
-    const uint32_t groups = GROUPS ? GROUPS : (uint32_t)groups_rt;
-    const uint32_t tg = blockIdx.x;
-    const uint32_t t = tg / groups;
-    const uint32_t g = tg - t * groups;
-    const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int64_t c0 = (int64_t)g * 128 + lane;
-    // Lanes past the end of a ragged last slice load chunk 0 instead and
-    // stage values that no thread sums: with no lane-dependent branch around
-    // the loads, every row load is issued before the first wait (guarded
-    // loads here each waited for the one before).
-    const int64_t c0a = c0 < nch ? c0 : 0, c0b = c0 + 64 < nch ? c0 + 64 : 0;
-    u32x4 v[SPW][2];
-    bool ok[SPW];
-#pragma unroll
-    for (int i = 0; i < SPW; ++i) {
-        const int n = j + kNodeWaves * i;
-        const int q = n < N ? node_pos[(int64_t)t * N + n] : -1;
-        ok[i] = q >= 0 && q < node_rows;
-        if (ok[i]) {
-            const u32x4* row = partial + (int64_t)q * nch;
-            v[i][0] = __builtin_nontemporal_load(row + c0a);
-            v[i][1] = __builtin_nontemporal_load(row + c0b);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < SPW; ++i) {
-        const int n = j + kNodeWaves * i;
-        if (n < N) {
-            if (ok[i]) {
-                stage[n * 128 + lane] = v[i][0];
-                stage[n * 128 + lane + 64] = v[i][1];
-            }
-            if (lane == 0) valid[n] = ok[i];
-        }
-    }
-    __syncthreads();
-    // kFoldWaves waves sum: thread i takes chunk i of the slice
-    if (j >= kFoldWaves) return;
-    const int i = threadIdx.x;
-    const int64_t c = (int64_t)g * 128 + i;
-    if (c >= nch) return;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int n = 0; n < N; ++n) {
-        if (!valid[n]) continue;
-        const u32x4 a = stage[n * 128 + i];
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            acc[2 * h] += __uint_as_float(a[h] << 16);
-            acc[2 * h + 1] += __uint_as_float(a[h] & 0xffff0000u);
-        }
-    }
-    u32x4 out;
-#pragma unroll
-    for (int h = 0; h < 4; ++h)
-        out[h] = pack_bf16_rne(acc[2 * h], acc[2 * h + 1]);
-    __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
-}
-
-template <int GROUPS>
-void launch_node_sum(const void* partial, const int32_t* node_pos, int64_t T, int N, int64_t nch,
-                     int64_t node_rows, void* y, hipStream_t s) {
-    const int64_t groups = (nch + 127) / 128;
-    if constexpr (GROUPS > 0) {
-        if (groups != GROUPS)
-            return launch_node_sum<GROUPS - 1>(partial, node_pos, T, N, nch, node_rows, y, s);
-    }
-    const dim3 block(kNodeWaves * 64);
-    const size_t lds = (size_t)N * 128 * sizeof(u32x4);
-    for_token_ranges(T, groups * kNodeWaves * 64, [&](int64_t t0, int64_t n) {
-        const dim3 grid((unsigned)(n * groups));
-        if (N <= 2 * kNodeWaves)
-            hipLaunchKernelGGL((node_sum_kernel<GROUPS, 2>), grid, block, lds, s,
-                               (const u32x4*)partial, node_pos + t0 * N, N, nch, node_rows,
-                               (int)groups, (u32x4*)y + t0 * nch);
-        else
-            hipLaunchKernelGGL((node_sum_kernel<GROUPS, 4>), grid, block, lds, s,
-                               (const u32x4*)partial, node_pos + t0 * N, N, nch, node_rows,
-                               (int)groups, (u32x4*)y + t0 * nch);
+                           T * K, node_rows, (int)groups, (u32x4*)partial,
+                           (u32x4*)y + t0 * nch);
     });
 }
 
@@ -427,10 +336,7 @@ cobalt_status launch_node_combine(const void* eo, const int32_t* pos, const int3
     const int64_t nch = d / 8;
     const int64_t node_rows = T * std::min(K, N);
     launch_node_fold<16>(eo, pos, assigned, gates, node_pos, T, K, N, gpn, nch, node_rows,
-                         partial, s);
-    COBALT_LAUNCH_CHECK();
-    // source side: y[t] = sum over n of partial[node_pos[t][n]], n increasing
-    launch_node_sum<16>(partial, node_pos, T, N, nch, node_rows, y, s);
+                         partial, y, s);
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;
 }
