@@ -19,8 +19,6 @@
 // Each expert of U_t then draws one of the cover's nodes holding it.
 // Step 2 (select execution ranks): every task draws one rank of its node
 // holding the expert. Draws hash the pair index with SplitMix64.
-#include <type_traits>
-
 #include "cover.hpp"
 #include "internal.hpp"
 
@@ -53,39 +51,6 @@ __device__ __forceinline__ uint32_t draw(uint64_t key, int64_t p, uint32_t strea
 __device__ __forceinline__ int kth_bit(uint32_t v, uint32_t k) {
     for (uint32_t i = 0; i < k; ++i) v &= v - 1u;
     return __builtin_ctz(v);
-}
-
-// A row of K ints in slots 0..K-1 of v, VEC ints per access (K is a multiple
-// of VEC and the row is aligned to VEC ints).
-template <int KM, int VEC>
-__device__ __forceinline__ void load_row(const int32_t* row, int K, int (&v)[KM]) {
-#pragma unroll
-    for (int j = 0; j < KM; j += VEC) {
-        if (j >= K) break;
-        if constexpr (VEC == 4) {
-            const int4 q = *reinterpret_cast<const int4*>(row + j);
-            v[j] = q.x; v[j + 1] = q.y; v[j + 2] = q.z; v[j + 3] = q.w;
-        } else if constexpr (VEC == 2) {
-            const int2 q = *reinterpret_cast<const int2*>(row + j);
-            v[j] = q.x; v[j + 1] = q.y;
-        } else {
-            v[j] = row[j];
-        }
-    }
-}
-
-template <int KM, int VEC>
-__device__ __forceinline__ void store_row(int32_t* row, int K, const int (&v)[KM]) {
-#pragma unroll
-    for (int j = 0; j < KM; j += VEC) {
-        if (j >= K) break;
-        if constexpr (VEC == 4)
-            *reinterpret_cast<int4*>(row + j) = make_int4(v[j], v[j + 1], v[j + 2], v[j + 3]);
-        else if constexpr (VEC == 2)
-            *reinterpret_cast<int2*>(row + j) = make_int2(v[j], v[j + 1]);
-        else
-            row[j] = v[j];
-    }
 }
 
 // KM: slots held in registers, at least K. VEC: ids read and ranks written
@@ -195,20 +160,12 @@ cobalt_status launch_assign(const DeviceLayout& L, const int32_t* topk, const in
     a.out = out;
     a.remote = remote;
     const unsigned blocks = (unsigned)((T + kAssignThreads - 1) / kAssignThreads);
-    const uintptr_t al = (uintptr_t)topk | (uintptr_t)out;
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kAssignThreads), 0, s, a);
-    };
-    auto by_row = [&](auto km) {
-        constexpr int KM = decltype(km)::value;
-        if (K % 4 == 0 && al % 16 == 0) return launch(assign_kernel<KM, 4>);
-        if (K % 2 == 0 && al % 8 == 0) return launch(assign_kernel<KM, 2>);
-        launch(assign_kernel<KM, 1>);
-    };
-    if (K <= 8)
-        by_row(std::integral_constant<int, 8>());
-    else
-        by_row(std::integral_constant<int, 16>());
+    // both rows are accessed alike: `out` decides where it is the less aligned
+    const uintptr_t o = (uintptr_t)out & 15u, q = (uintptr_t)topk & 15u;
+    by_row(K, (const void*)(o | q), [&](auto km, auto vec) {
+        hipLaunchKernelGGL((assign_kernel<decltype(km)::value, decltype(vec)::value>),
+                           dim3(blocks), dim3(kAssignThreads), 0, s, a);
+    });
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;
 }

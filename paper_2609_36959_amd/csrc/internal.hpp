@@ -5,6 +5,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <type_traits>
 
 #include "cobalt.h"
 
@@ -33,6 +34,57 @@ __device__ __forceinline__ void store_stream(const u32x4& v, void* base, int32_t
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(base, (short)0, bytes, 0x00020000);
     __builtin_amdgcn_raw_buffer_store_b128(v, rs, offset, 0, kNt);
+}
+
+// A row of K ints in slots 0..K-1 of v, VEC ints per access (K is a multiple
+// of VEC and the row is aligned to VEC ints).
+template <int KM, int VEC>
+__device__ __forceinline__ void load_row(const int32_t* row, int K, int (&v)[KM]) {
+#pragma unroll
+    for (int j = 0; j < KM; j += VEC) {
+        if (j >= K) continue;
+        if constexpr (VEC == 4) {
+            const int4 q = *reinterpret_cast<const int4*>(row + j);
+            v[j] = q.x; v[j + 1] = q.y; v[j + 2] = q.z; v[j + 3] = q.w;
+        } else if constexpr (VEC == 2) {
+            const int2 q = *reinterpret_cast<const int2*>(row + j);
+            v[j] = q.x; v[j + 1] = q.y;
+        } else {
+            v[j] = row[j];
+        }
+    }
+}
+
+template <int KM, int VEC>
+__device__ __forceinline__ void store_row(int32_t* row, int K, const int (&v)[KM]) {
+#pragma unroll
+    for (int j = 0; j < KM; j += VEC) {
+        if (j >= K) continue;
+        if constexpr (VEC == 4)
+            *reinterpret_cast<int4*>(row + j) = make_int4(v[j], v[j + 1], v[j + 2], v[j + 3]);
+        else if constexpr (VEC == 2)
+            *reinterpret_cast<int2*>(row + j) = make_int2(v[j], v[j + 1]);
+        else
+            row[j] = v[j];
+    }
+}
+
+// Calls f(KM, VEC) for rows of K ints at `p`: KM slots in registers, VEC ints
+// per access.
+template <typename F>
+void by_row(int K, const void* p, F&& f) {
+    auto vec = [&](auto km) {
+        if (K % 4 == 0 && ((uintptr_t)p & 15u) == 0)
+            f(km, std::integral_constant<int, 4>());
+        else if (K % 2 == 0 && ((uintptr_t)p & 7u) == 0)
+            f(km, std::integral_constant<int, 2>());
+        else
+            f(km, std::integral_constant<int, 1>());
+    };
+    if (K <= 8)
+        vec(std::integral_constant<int, 8>());
+    else
+        vec(std::integral_constant<int, 16>());
 }
 
 struct DeviceLayout {
@@ -95,6 +147,14 @@ cobalt_status launch_dispatch(const int32_t* assigned, const int32_t* src, int64
 // (COBALT_DISPATCH_NOALLOC_SCRATCH_BYTES bytes, 256-byte aligned); looked up
 // on the first call on each device, allocates nothing.
 cobalt_status dispatch_noalloc_scratch(void** out);
+// Counts, offsets and rows of a dispatch (layout.hip).
+cobalt_status launch_layout(const int32_t* assigned, const int32_t* src, int64_t T, int K, int G,
+                            int32_t* counts, int64_t* offsets, int32_t* pos, void* ws,
+                            hipStream_t s);
+cobalt_status launch_node_layout(const int32_t* assigned, const int32_t* src, int64_t T, int K,
+                                 int N, int g, int32_t* counts, int64_t* offsets,
+                                 int32_t* node_pos, uint32_t* fwd, int32_t* row_token, void* ws,
+                                 hipStream_t s);
 size_t node_dispatch_workspace_bytes(int64_t T, int N, int G);
 cobalt_status launch_node_dispatch(const int32_t* assigned, const int32_t* src, int64_t T, int K,
                                    int N, int g, const void* x, int64_t d, int32_t* counts,
