@@ -36,6 +36,14 @@ __device__ __forceinline__ void store_stream(const u32x4& v, void* base, int32_t
     __builtin_amdgcn_raw_buffer_store_b128(v, rs, offset, 0, kNt);
 }
 
+// x / y for 0 <= x < 2^17 and 1 <= y: (x + 1/2) / y lies at least 1 / (2y)
+// from an integer, and the product is off by less than x / y * 2^-22.
+struct SmallDiv {
+    float inv;
+    __device__ __forceinline__ int operator()(int x) const { return (int)(((float)x + 0.5f) * inv); }
+};
+__host__ __device__ inline SmallDiv divide_by(int64_t v) { return {1.0f / (float)v}; }
+
 // A row of K ints in slots 0..K-1 of v, VEC ints per access (K is a multiple
 // of VEC and the row is aligned to VEC ints).
 template <int KM, int VEC>

@@ -244,13 +244,6 @@ __global__ __launch_bounds__(kThreads) void tile_rank_kernel(
 }
 
 // --------------------------------------------------- whole-call workgroups
-// x / y for 0 <= x < 2^17 and 1 <= y: (x + 1/2) / y lies at least 1 / (2y)
-// from an integer, and the product is off by less than x / y * 2^-22.
-struct SmallDiv {
-    float inv;
-    __device__ __forceinline__ int operator()(int x) const { return (int)(((float)x + 0.5f) * inv); }
-};
-
 // Turns the counts in table[R][C] into first rows: the offset of each bucket
 // in row-major order, less its column's count in the rows above, plus
 // prior[c]. With `write`, also writes the offsets, and the counts if asked
@@ -924,8 +917,6 @@ __global__ __launch_bounds__(kThreads) void small_node_layout_kernel(
 }
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
-
-SmallDiv divide_by(int64_t v) { return {1.0f / (float)v}; }
 
 }  // namespace
 

@@ -14,19 +14,23 @@
 //   count   grid = chunks x bands. A workgroup takes a contiguous chunk of
 //           tokens and keeps its band's bins, and the counts of the experts
 //           e = b (mod nb), in LDS. Each thread loads a token's ids (16-byte
-//           loads for K = 8), sorts them in registers, and for every sorted
-//           slot a whose expert is in the band adds one to the bins (e[a],
-//           e[b]) of the later slots, with LDS atomics. The band's bins are
-//           then written to the chunk's slot of the workspace, as uint16
-//           where no bin of a chunk can pass 65535, else as uint32.
-//   reduce  sixteen lanes per group of eight band bins sum the group over
-//           the chunks (lane k takes chunks k, k + 16, ..., one 16-byte load
-//           of eight uint16 bins each), add pairwise across lanes k and
-//           k + 8, then exchange halves in three shuffle rounds so that lane
-//           k < 8 ends with the total of bin k, which it adds to coact[i][j]
-//           and coact[j][i]. Other lanes do the same for expert_count. Every
-//           output element has exactly one writer, so the result does not
-//           depend on scheduling.
+//           loads where K and the address allow it), sorts them in registers,
+//           and for every sorted slot a whose expert is in the band adds one
+//           to the bins (e[a], e[b]) of the later slots, with LDS atomics.
+//           The band's bins are then written to the chunk's slot of the
+//           workspace, as uint16 where no bin of a chunk can pass 65535,
+//           else as uint32.
+//   reduce  eight or sixteen lanes per group of eight band bins sum the group
+//           over the chunks (lane k takes chunks k, k + lanes, ..., one
+//           16-byte load of eight uint16 bins each), add pairwise across
+//           lanes k and k + 8, then exchange halves in three shuffle rounds
+//           so that lane k < 8 ends with the total of bin k, which it adds to
+//           coact[i][j] and coact[j][i]. Other lanes do the same for
+//           expert_count. Every output element has exactly one writer, so the
+//           result does not depend on scheduling. With few chunks the
+//           shuffles and the row search are most of the work, so the fewer
+//           lanes, with the row from a square root, serve up to kFewChunks
+//           (E = 1024, 16384 tokens: 24.5 to 22.8 us a call).
 //
 // Checks. Ids outside [0, E) count nowhere. A token that repeats an id adds
 // the product of the multiplicities to a pair, and m (m - 1) to the
@@ -37,11 +41,22 @@
 // normal case, found with one ballot), the wave adds its pairs without
 // per-pair tests.
 //
-// Small calls (one band, at most kDirectUpdates bin updates over all
-// chunks) skip the reduce: each count workgroup adds its nonzero bins
-// straight into coact and expert_count with integer atomics, whose sums do
-// not depend on their order. That saves the second launch, most of the time
-// of such a call.
+// Small calls (E up to kDirectE, kDirectUpdates elements over all chunks)
+// skip the reduce: each count workgroup goes through coact's elements and
+// adds its nonzero bins with integer atomics, whose sums do not depend on
+// their order, a whole line of a row per wave. 4096 tokens with E = 16, K = 2
+// take 3.9 us so (7.4 with the reduce; 12.8 when the bins of the triangle
+// were added one by one), 256 with E = 128, K = 8 7.4 (8.4; 11.1), 16384 with
+// E = 64, K = 6 6.2 (8.9; 15.9). At E = 256 one workgroup's walk over 65536
+// elements takes longer than the reduce (20.9 against 12.4 us for 256
+// tokens).
+//
+// Chunks. A workgroup's LDS atomics queue on its CU, so chunks are short
+// until the partials they add cost as much: 512 tokens (256 up to kDirectE),
+// at most 128 chunks, and with many bands at most kMaxGroups workgroups:
+// E = 1024, 131072 tokens take 56 us with 33 chunks (the uint16 bound) of 16
+// bands against 101 with 128; E = 256, 4096 tokens 14.0 us in 8 chunks
+// against 16.8 in 4.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -56,14 +71,16 @@ namespace {
 
 constexpr int kCountThreads = 1024;
 constexpr int kReduceThreads = 256;
-constexpr int kReduceLanes = 16;  // lanes per group of eight bins (and per count)
 constexpr int kMaxLgBands = 12;
-constexpr int64_t kTokensPerChunk = 1024;
+constexpr int64_t kTokensPerChunk = 512;
 constexpr int64_t kMaxChunks = 128;
 constexpr int64_t kMaxChunks16 = 128;  // more chunks allowed to keep uint16 partials
 constexpr int kParBands = 2;            // bands for parallelism on large calls
 constexpr int64_t kParPairs = 1 << 18;  // T*K from which bands are used for parallelism
-constexpr int64_t kDirectUpdates = 65536;
+constexpr int64_t kMaxGroups = 256;
+constexpr int kDirectE = 128;
+constexpr int64_t kDirectUpdates = 262144;
+constexpr int kFewChunks = 32;
 
 struct Plan {
     int nchunks;
@@ -100,7 +117,21 @@ int64_t cnt_words(int E, int nb) { return round_up((E + nb - 1) / nb, 4); }
 
 bool make_plan(int64_t T, int64_t K, int E, int lds_bytes, Plan* p) {
     p->words = (int64_t)E * (E - 1) / 2;
-    p->nchunks = (int)std::min<int64_t>(kMaxChunks, std::max<int64_t>(1, T / kTokensPerChunk));
+    const int64_t lds_words = lds_bytes / 4;
+    auto fits = [&](int l) { return hist_words(E, 1 << l) + 2 * cnt_words(E, 1 << l) <= lds_words; };
+    // fewest bands whose largest band and counts fit the LDS
+    int lgb = 0;
+    while (lgb <= kMaxLgBands && !fits(lgb)) ++lgb;
+    if (lgb > kMaxLgBands) return false;
+    // large calls: more bands, for more workgroups (at most one row per band)
+    if (T * K >= kParPairs)
+        while ((1 << lgb) < kParBands && (1 << (lgb + 1)) <= std::max(E - 1, 1)) ++lgb;
+    // Chunks of about kTokensPerChunk tokens, up to kMaxChunks, and no more
+    // than make kMaxGroups workgroups: each chunk adds a whole triangle to
+    // the partials that are written and read back.
+    const int64_t most = std::max<int64_t>(1, std::min(kMaxChunks, kMaxGroups >> lgb));
+    p->nchunks = (int)std::min(most, std::max<int64_t>(1, T / (E <= kDirectE ? kTokensPerChunk / 2
+                                                                            : kTokensPerChunk)));
     p->tok_per_chunk = std::max<int64_t>(1, (T + p->nchunks - 1) / p->nchunks);
     // A token adds at most floor(K/2) * ceil(K/2) to one bin (two experts,
     // each repeated), so a chunk's bins fit in uint16 when its tokens times
@@ -116,15 +147,6 @@ bool make_plan(int64_t T, int64_t K, int E, int lds_bytes, Plan* p) {
             p->u16 = p->tok_per_chunk * maxpair <= 65535;
         }
     }
-    const int64_t lds_words = lds_bytes / 4;
-    auto fits = [&](int l) { return hist_words(E, 1 << l) + 2 * cnt_words(E, 1 << l) <= lds_words; };
-    // fewest bands whose largest band and counts fit the LDS
-    int lgb = 0;
-    while (lgb <= kMaxLgBands && !fits(lgb)) ++lgb;
-    if (lgb > kMaxLgBands) return false;
-    // large calls: more bands, for more workgroups (at most one row per band)
-    if (T * K >= kParPairs)
-        while ((1 << lgb) < kParBands && (1 << (lgb + 1)) <= std::max(E - 1, 1)) ++lgb;
     p->lgb = lgb;
     const int nb = 1 << lgb;
     p->band_stride = hist_words(E, nb);
@@ -135,24 +157,16 @@ bool make_plan(int64_t T, int64_t K, int E, int lds_bytes, Plan* p) {
     return true;
 }
 
-// Row i of triangle bin w (one band): the largest i with i-th row start <= w.
-__device__ __forceinline__ int32_t tri_row(int32_t w, int32_t E) {
-    const int32_t words = E * (E - 1) / 2;
-    const int32_t r = words - 1 - w;  // index counted back from the last bin
-    int32_t q = (int32_t)((sqrtf(8.0f * (float)r + 1.0f) - 1.0f) * 0.5f);
-    while ((q + 1) * (q + 2) / 2 <= r) ++q;
-    while (q > 0 && q * (q + 1) / 2 > r) --q;
-    return E - 2 - q;
-}
-
-// Local row of bin w of band b: the last r with off_b(r) <= w.
+// Local row of bin w of band b: the last r with off_b(r) <= w, from the root
+// of the quadratic off_b, set right by a step or two where it is rounded.
 __device__ __forceinline__ int32_t band_row_of(int32_t E, int32_t nb, int32_t b, int32_t w) {
-    int32_t lo = 0, hi = band_rows(E, nb, b) - 1;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) / 2;
-        if (band_off(E, nb, b, mid) <= w) lo = mid; else hi = mid - 1;
-    }
-    return lo;
+    const float h = (float)(2 * (E - 1 - b) + nb);
+    const float q = fmaxf(h * h - 8.0f * (float)nb * (float)w, 0.0f);
+    int32_t r = (int32_t)((h - sqrtf(q)) / (float)(2 * nb));
+    r = max(0, min(r, band_rows(E, nb, b) - 1));
+    while (r > 0 && band_off(E, nb, b, r) > w) --r;
+    while (r + 1 < band_rows(E, nb, b) && band_off(E, nb, b, r + 1) <= w) ++r;
+    return r;
 }
 
 __device__ __forceinline__ void cswap(int& a, int& b) {
@@ -161,44 +175,34 @@ __device__ __forceinline__ void cswap(int& a, int& b) {
     b = hi;
 }
 
-// Sorts e[0..KM) ascending: Batcher's odd-even merge sort network for 8
-// (19 comparators), odd-even transposition otherwise.
+// Sorts e[0..KM) ascending, KM a power of two: Batcher's odd-even merge sort
+// network (5 comparators for 4, 19 for 8, 63 for 16).
 template <int KM>
 __device__ __forceinline__ void sort_ids(int (&e)[KM]) {
-    if constexpr (KM == 8) {
-        cswap(e[0], e[1]); cswap(e[2], e[3]); cswap(e[4], e[5]); cswap(e[6], e[7]);
-        cswap(e[0], e[2]); cswap(e[1], e[3]); cswap(e[4], e[6]); cswap(e[5], e[7]);
-        cswap(e[1], e[2]); cswap(e[5], e[6]);
-        cswap(e[0], e[4]); cswap(e[1], e[5]); cswap(e[2], e[6]); cswap(e[3], e[7]);
-        cswap(e[2], e[4]); cswap(e[3], e[5]);
-        cswap(e[1], e[2]); cswap(e[3], e[4]); cswap(e[5], e[6]);
-    } else {
 #pragma unroll
-        for (int r = 0; r < KM; ++r) {
+    for (int p = 1; p < KM; p *= 2)
 #pragma unroll
-            for (int a = r & 1; a + 1 < KM; a += 2) cswap(e[a], e[a + 1]);
-        }
-    }
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int j = k % p; j + k < KM; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < KM && (i + j) / (2 * p) == (i + j + k) / (2 * p))
+                        cswap(e[i + j], e[i + j + k]);
 }
 
 // Loads token t's ids into e (INT_MAX past K).
-template <int KC, bool kVec, int KM>
+template <int KM, int VEC>
 __device__ __forceinline__ void load_ids(const int32_t* __restrict__ topk, int64_t t, int K,
                                          int (&e)[KM]) {
-    if constexpr (kVec) {
-        const int4* p = reinterpret_cast<const int4*>(topk + t * 8);
-        const int4 v0 = p[0], v1 = p[1];
-        e[0] = v0.x; e[1] = v0.y; e[2] = v0.z; e[3] = v0.w;
-        e[4] = v1.x; e[5] = v1.y; e[6] = v1.z; e[7] = v1.w;
-    } else {
 #pragma unroll
-        for (int a = 0; a < KM; ++a) e[a] = a < K ? topk[t * K + a] : INT_MAX;
-    }
+    for (int a = 0; a < KM; ++a) e[a] = INT_MAX;
+    load_row<KM, VEC>(topk + t * K, K, e);
 }
 
 // One token of the count kernel: its counts, pairs and repeats in band `band`.
-template <int KC, int KM>
-__device__ __forceinline__ void count_token(int (&e)[KM], int E, int lgb, int band,
+template <int KM>
+__device__ __forceinline__ void count_token(int (&e)[KM], int K, int E, int lgb, int band,
                                             int32_t row_len0, uint32_t* hist, uint32_t* cnt,
                                             uint32_t* diag) {
     const int nb = 1 << lgb;
@@ -209,23 +213,21 @@ __device__ __forceinline__ void count_token(int (&e)[KM], int E, int lgb, int ba
     for (int a = 0; a < KM; ++a)
         if (e[a] != INT_MAX && (e[a] & (nb - 1)) == band) atomicAdd(&cnt[e[a] >> lgb], 1u);
     sort_ids<KM>(e);
-    bool fast = false;
-    if constexpr (KC == 8) {
-        // K distinct ids in range: strictly increasing, the last not INT_MAX
-        bool ok = e[KM - 1] != INT_MAX;
+    // K distinct ids in range: strictly increasing, the K-th not INT_MAX
+    bool ok = true;
 #pragma unroll
-        for (int a = 0; a + 1 < KM; ++a) ok = ok && e[a] < e[a + 1];
-        fast = __builtin_amdgcn_ballot_w64(!ok) == 0;  // one value for the wave
-    }
-    if (fast) {
+    for (int a = 0; a < KM; ++a)
+        if (a < K) ok = ok && e[a] != INT_MAX && (a == 0 || e[a > 0 ? a - 1 : 0] < e[a]);
+    if (__builtin_amdgcn_ballot_w64(!ok) == 0) {  // one value for the wave
 #pragma unroll
         for (int a = 0; a + 1 < KM; ++a) {
             const int i = e[a];
-            if ((i & (nb - 1)) != band) continue;
+            if (a + 1 >= K || (i & (nb - 1)) != band) continue;
             const int32_t r = i >> lgb;
             const int32_t base = r * row_len0 - nb * (r * (r - 1) / 2) - i - 1;
 #pragma unroll
-            for (int b = a + 1; b < KM; ++b) atomicAdd(&hist[base + e[b]], 1u);
+            for (int b = a + 1; b < KM; ++b)
+                if (b < K) atomicAdd(&hist[base + e[b]], 1u);
         }
     } else {
 #pragma unroll
@@ -249,24 +251,21 @@ __device__ __forceinline__ void count_token(int (&e)[KM], int E, int lgb, int ba
     }
 }
 
-// KC = compile-time K (0: any K up to 16, read at run time); kVec: K = 8
-// and a 16-byte aligned topk, read with two 16-byte loads per token. Ids
-// outside [0, E) sort last as INT_MAX and count nowhere. U16: partial bins
-// written as uint16. A thread takes two tokens per iteration and issues
-// both loads before either is counted.
-template <int KC, bool kVec, bool U16>
+// KM: ids held in registers, at least K (kFull: exactly K, so that no slot is
+// tested for); VEC: ids per load (load_row). Ids outside [0, E) sort last as INT_MAX and count nowhere. U16: partial bins
+// written as uint16. A thread takes two tokens per iteration and issues both
+// loads before either is counted.
+template <int KM, int VEC, bool kFull, bool U16>
 __global__ __launch_bounds__(kCountThreads) void coact_count_kernel(
     const int32_t* __restrict__ topk, int64_t T, int Kr, int E, int lgb, int nchunks,
     int64_t tok_per_chunk, int64_t band_stride, int cnt_off, void* __restrict__ part,
     uint32_t* __restrict__ cpart, bool direct, uint32_t* __restrict__ coact,
     uint32_t* __restrict__ count) {
-    constexpr int KM = KC ? KC : kMaxK;
-    const int K = KC ? KC : Kr;
+    const int K = kFull ? KM : Kr;
     extern __shared__ uint32_t lds[];
     const int nb = 1 << lgb;
     const int chunk = blockIdx.x % nchunks;
     const int band = blockIdx.x / nchunks;
-    const int32_t nbins = band_words(E, nb, band);
     const int32_t ncnt = band < E ? (E - band + nb - 1) / nb : 0;
     const int32_t row_len0 = E - 1 - band;  // length of local row 0
     uint32_t* hist = lds;
@@ -284,31 +283,33 @@ __global__ __launch_bounds__(kCountThreads) void coact_count_kernel(
     for (int64_t t = t0 + threadIdx.x; t < t1; t += 2 * kCountThreads) {
         const int64_t u = t + kCountThreads;
         int e[KM], f[KM];
-        load_ids<KC, kVec>(topk, t, K, e);
-        if (u < t1) load_ids<KC, kVec>(topk, u, K, f);
-        count_token<KC>(e, E, lgb, band, row_len0, hist, cnt, diag);
-        if (u < t1) count_token<KC>(f, E, lgb, band, row_len0, hist, cnt, diag);
+        load_ids<KM, VEC>(topk, t, K, e);
+        if (u < t1) load_ids<KM, VEC>(topk, u, K, f);
+        count_token<KM>(e, K, E, lgb, band, row_len0, hist, cnt, diag);
+        if (u < t1) count_token<KM>(f, K, E, lgb, band, row_len0, hist, cnt, diag);
     }
     __syncthreads();
+
+    if (direct) {  // one band: the chunk's bins go straight to the outputs
+        // Thread by thread over coact's elements, so that both triangles are
+        // added to in whole lines.
+        const SmallDiv by_e = divide_by(E);
+        for (int32_t x = threadIdx.x; x < E * E; x += kCountThreads) {
+            const int32_t i = by_e(x), j = x - i * E;
+            const int32_t lo = min(i, j), hi = max(i, j);
+            const uint32_t v = i == j ? diag[i] : hist[band_off(E, 1, 0, lo) + hi - lo - 1];
+            if (v) atomicAdd(&coact[x], v);
+        }
+        for (int32_t k = threadIdx.x; k < ncnt; k += kCountThreads)
+            if (count && cnt[k]) atomicAdd(&count[k], cnt[k]);
+        return;
+    }
 
     // Write-out: thread g takes bins [8g, 8g + 8).
     const int32_t groups = (int32_t)(band_stride / 8);
     for (int32_t g = threadIdx.x; g < groups; g += kCountThreads) {
         const u32x4 lo = *reinterpret_cast<const u32x4*>(lds + g * 8);
         const u32x4 hi = *reinterpret_cast<const u32x4*>(lds + g * 8 + 4);
-        if (direct) {  // one band: the chunk's bins go straight to the outputs
-            const uint32_t v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int32_t bin = g * 8 + k;
-                if (v[k] == 0 || bin >= nbins) continue;
-                const int32_t i = tri_row(bin, E);
-                const int32_t j = bin - band_off(E, 1, 0, i) + i + 1;
-                atomicAdd(&coact[(int64_t)i * E + j], v[k]);
-                atomicAdd(&coact[(int64_t)j * E + i], v[k]);
-            }
-            continue;
-        }
         const int64_t at = ((int64_t)band * nchunks + chunk) * band_stride + g * 8;
         if constexpr (U16) {
             const u32x4 packed = {lo.x | (lo.y << 16), lo.z | (lo.w << 16), hi.x | (hi.y << 16),
@@ -321,12 +322,7 @@ __global__ __launch_bounds__(kCountThreads) void coact_count_kernel(
         }
     }
     for (int32_t k = threadIdx.x; k < ncnt; k += kCountThreads) {
-        const uint32_t v = cnt[k];
-        if (direct) {
-            if (count && v) atomicAdd(&count[k], v);
-        } else {
-            cpart[(int64_t)chunk * E + k * nb + band] = v;
-        }
+        cpart[(int64_t)chunk * E + k * nb + band] = cnt[k];
         const int64_t ex = (int64_t)k * nb + band;
         if (diag[k]) atomicAdd(&coact[ex * E + ex], diag[k]);
     }
@@ -335,7 +331,7 @@ __global__ __launch_bounds__(kCountThreads) void coact_count_kernel(
 // Items [0, nb * band_stride / 8) are groups of eight band bins, then E
 // expert counts; kReduceLanes lanes per item, lane k summing chunks k,
 // k + kReduceLanes, ...
-template <bool U16>
+template <bool U16, int kReduceLanes>
 __global__ __launch_bounds__(kReduceThreads) void coact_reduce_kernel(
     const void* __restrict__ part, const uint32_t* __restrict__ cpart, int E, int lgb,
     int nchunks, int64_t band_stride, bool do_count, uint32_t* __restrict__ coact,
@@ -449,54 +445,60 @@ cobalt_status launch_coact_stats(const int32_t* topk, int64_t T, int K, int E, u
     if (!make_plan(T, K, E, di.lds_bytes, &p)) return COBALT_EUNSUPPORTED;
     if (ws_bytes < p.part_bytes + p.count_bytes) return COBALT_EINVAL;
     const int nb = 1 << p.lgb;
-    const bool direct = nb == 1 && p.nchunks * (p.words + E) <= kDirectUpdates;
+    const bool direct = nb == 1 && E <= kDirectE && (int64_t)p.nchunks * E * E <= kDirectUpdates;
     void* part = ws;
     uint32_t* cpart = (uint32_t*)((char*)ws + p.part_bytes);
-    // The LDS limit of each kernel variant is raised to the device maximum
-    // once per device (host-side only, so the calls stay capturable).
-    auto launch = [&](auto kernel, int variant) -> cobalt_status {
+    // The LDS limit of each kernel is raised to the device maximum once per
+    // device (host-side only, so the calls stay capturable).
+    cobalt_status st = COBALT_OK;
+    auto launch = [&](auto kernel) {
         static std::mutex mu;
-        static std::set<std::pair<int, int>> raised;
+        static std::set<std::pair<const void*, int>> raised;
         int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return COBALT_EHIP;
+        if (hipGetDevice(&dev) != hipSuccess) {
+            st = COBALT_EHIP;
+            return;
+        }
         {
             std::lock_guard<std::mutex> lock(mu);
-            if (!raised.count({variant, dev})) {
+            if (!raised.count({(const void*)kernel, dev})) {
                 if (hipFuncSetAttribute((const void*)kernel,
                                         hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        di.lds_bytes) != hipSuccess)
-                    return COBALT_EHIP;
-                raised.insert({variant, dev});
+                                        di.lds_bytes) != hipSuccess) {
+                    st = COBALT_EHIP;
+                    return;
+                }
+                raised.insert({(const void*)kernel, dev});
             }
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)(p.nchunks * nb)), dim3(kCountThreads),
                            p.lds_bytes, s, topk, T, K, E, p.lgb, p.nchunks, p.tok_per_chunk,
                            p.band_stride, p.cnt_off, part, cpart, direct, coact, count);
-        return COBALT_OK;
     };
-    const bool vec = K == 8 && ((uintptr_t)topk & 15u) == 0;
-    cobalt_status st;
-    if (p.u16)
-        st = vec      ? launch(coact_count_kernel<8, true, true>, 0)
-             : K == 8 ? launch(coact_count_kernel<8, false, true>, 1)
-                      : launch(coact_count_kernel<0, false, true>, 2);
-    else
-        st = vec      ? launch(coact_count_kernel<8, true, false>, 3)
-             : K == 8 ? launch(coact_count_kernel<8, false, false>, 4)
-                      : launch(coact_count_kernel<0, false, false>, 5);
+    by_row(K, topk, [&](auto km, auto vec) {
+        constexpr int KM = decltype(km)::value, V = decltype(vec)::value;
+        if (K == KM)
+            p.u16 ? launch(coact_count_kernel<KM, V, true, true>)
+                  : launch(coact_count_kernel<KM, V, true, false>);
+        else
+            p.u16 ? launch(coact_count_kernel<KM, V, false, true>)
+                  : launch(coact_count_kernel<KM, V, false, false>);
+    });
     if (st != COBALT_OK) return st;
     COBALT_LAUNCH_CHECK();
     if (direct) return COBALT_OK;
     const int64_t items = (int64_t)nb * (p.band_stride / 8) + (count ? E : 0);
-    const dim3 grid((unsigned)((items * kReduceLanes + kReduceThreads - 1) / kReduceThreads));
-    if (p.u16)
-        hipLaunchKernelGGL(coact_reduce_kernel<true>, grid, dim3(kReduceThreads), 0, s, part,
-                           cpart, E, p.lgb, p.nchunks, p.band_stride, count != nullptr, coact,
-                           count);
+    auto reduce = [&](auto kernel, int lanes) {
+        hipLaunchKernelGGL(kernel,
+                           dim3((unsigned)((items * lanes + kReduceThreads - 1) / kReduceThreads)),
+                           dim3(kReduceThreads), 0, s, part, cpart, E, p.lgb, p.nchunks,
+                           p.band_stride, count != nullptr, coact, count);
+    };
+    if (p.nchunks <= kFewChunks)
+        p.u16 ? reduce(coact_reduce_kernel<true, 8>, 8) : reduce(coact_reduce_kernel<false, 8>, 8);
     else
-        hipLaunchKernelGGL(coact_reduce_kernel<false>, grid, dim3(kReduceThreads), 0, s, part,
-                           cpart, E, p.lgb, p.nchunks, p.band_stride, count != nullptr, coact,
-                           count);
+        p.u16 ? reduce(coact_reduce_kernel<true, 16>, 16)
+              : reduce(coact_reduce_kernel<false, 16>, 16);
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;
 }
