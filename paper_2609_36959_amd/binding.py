@@ -84,28 +84,38 @@ def lib() -> ctypes.CDLL:
 
 
 def _call(name: str, *args) -> None:
-    st = getattr(lib(), name)(*args)
+    st = getattr(_lib or lib(), name)(*args)
     if st != 0:
         raise CobaltError(name, st)
 
 
+# torch.cuda.current_stream() builds a Stream object, 2.8 us of a call that
+# takes 4 us with its launch; the raw handle of the same stream takes 0.1 us.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_device = torch._C._cuda_getDevice
+
+
 def _stream(stream) -> Optional[int]:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _dev(t: Optional[torch.Tensor], name: str, dtypes, shape=None) -> Optional[int]:
     if t is None:
         return None
+    if t.is_cuda and t.dtype in dtypes and (shape is None or t.shape == shape) \
+            and t.is_contiguous():
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if t.dtype not in dtypes:
         raise ValueError(f"{name} must have dtype in {dtypes}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    return t.data_ptr()
+    raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
 I32 = (torch.int32,)
@@ -196,10 +206,8 @@ def cobalt_dispatch_pack(assigned_rank: torch.Tensor, src_rank: Optional[torch.T
                          stream=None) -> None:
     T, K = assigned_rank.shape
     d = 0 if x is None else x.shape[1]
-    if x is not None:
-        _dev(x, "x", BF16, (T, d))
     _call("cobalt_dispatch_pack", _dev(assigned_rank, "assigned_rank", I32),
-          _dev(src_rank, "src_rank", I32, (T,)), T, K, G, _dev(x, "x", BF16), d,
+          _dev(src_rank, "src_rank", I32, (T,)), T, K, G, _dev(x, "x", BF16, (T, d)), d,
           _dev(send_counts, "send_counts", I32, (G, G)),
           _dev(send_offsets, "send_offsets", I64, (G * G + 1,)),
           _dev(pos, "pos", I32, (T, K)),
@@ -219,10 +227,8 @@ def cobalt_dispatch_pack_noalloc(assigned_rank: torch.Tensor, src_rank: Optional
     workspace; calls that may overlap on one GPU must not be issued."""
     T, K = assigned_rank.shape
     d = 0 if x is None else x.shape[1]
-    if x is not None:
-        _dev(x, "x", BF16, (T, d))
     _call("cobalt_dispatch_pack_noalloc", _dev(assigned_rank, "assigned_rank", I32),
-          _dev(src_rank, "src_rank", I32, (T,)), T, K, G, _dev(x, "x", BF16), d,
+          _dev(src_rank, "src_rank", I32, (T,)), T, K, G, _dev(x, "x", BF16, (T, d)), d,
           _dev(send_counts, "send_counts", I32, (G, G)),
           _dev(send_offsets, "send_offsets", I64, (G * G + 1,)),
           _dev(pos, "pos", I32, (T, K)),
@@ -245,10 +251,9 @@ def cobalt_node_dispatch_pack(assigned_rank: torch.Tensor, src_rank: Optional[to
     G = N * gpus_per_node
     cap = T * min(K, N)
     d = 0 if x is None else x.shape[1]
-    if x is not None:
-        _dev(x, "x", BF16, (T, d))
     _call("cobalt_node_dispatch_pack", _dev(assigned_rank, "assigned_rank", I32),
-          _dev(src_rank, "src_rank", I32, (T,)), T, K, N, gpus_per_node, _dev(x, "x", BF16), d,
+          _dev(src_rank, "src_rank", I32, (T,)), T, K, N, gpus_per_node,
+          _dev(x, "x", BF16, (T, d)), d,
           _dev(node_counts, "node_counts", I32, (G, N)),
           _dev(node_offsets, "node_offsets", I64, (G * N + 1,)),
           _dev(node_pos, "node_pos", I32, (T, N)),
