@@ -36,6 +36,18 @@ __device__ __forceinline__ void store_stream(const u32x4& v, void* base, int32_t
     __builtin_amdgcn_raw_buffer_store_b128(v, rs, offset, 0, kNt);
 }
 
+// Store of 16 bytes at base + offset that goes through the L2 as it is made
+// (sc1), for data that the next kernel reads on all XCDs: plain stores leave
+// the lines dirty in the writer's L2, and the kernel's end waits while all of
+// them are written back.
+__device__ __forceinline__ void store_through(const u32x4& v, void* base, int32_t bytes,
+                                              int32_t offset) {
+    constexpr int kSc1 = 16;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(base, (short)0, bytes, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(v, rs, offset, 0, kSc1);
+}
+
 // x / y for 0 <= x < 2^17 and 1 <= y: (x + 1/2) / y lies at least 1 / (2y)
 // from an integer, and the product is off by less than x / y * 2^-22.
 struct SmallDiv {

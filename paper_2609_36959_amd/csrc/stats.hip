@@ -305,20 +305,23 @@ __global__ __launch_bounds__(kCountThreads) void coact_count_kernel(
         return;
     }
 
-    // Write-out: thread g takes bins [8g, 8g + 8).
+    // Write-out: thread g takes bins [8g, 8g + 8). Written through the L2:
+    // the count kernel takes 21.0 us instead of 23.9 on T = 262144, E = 384
+    // (18.8 MB of partials), 12.1 instead of 14.0 on T = 131072, E = 256.
     const int32_t groups = (int32_t)(band_stride / 8);
+    const int64_t at = ((int64_t)band * nchunks + chunk) * band_stride;
+    const int32_t bytes = (int32_t)band_stride * (U16 ? 2 : 4);
+    void* out = static_cast<char*>(part) + at * (U16 ? 2 : 4);
     for (int32_t g = threadIdx.x; g < groups; g += kCountThreads) {
         const u32x4 lo = *reinterpret_cast<const u32x4*>(lds + g * 8);
         const u32x4 hi = *reinterpret_cast<const u32x4*>(lds + g * 8 + 4);
-        const int64_t at = ((int64_t)band * nchunks + chunk) * band_stride + g * 8;
         if constexpr (U16) {
             const u32x4 packed = {lo.x | (lo.y << 16), lo.z | (lo.w << 16), hi.x | (hi.y << 16),
                                   hi.z | (hi.w << 16)};
-            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(part) + at) = packed;
+            store_through(packed, out, bytes, g * 16);
         } else {
-            u32x4* out = reinterpret_cast<u32x4*>(static_cast<uint32_t*>(part) + at);
-            out[0] = lo;
-            out[1] = hi;
+            store_through(lo, out, bytes, g * 32);
+            store_through(hi, out, bytes, g * 32 + 16);
         }
     }
     for (int32_t k = threadIdx.x; k < ncnt; k += kCountThreads) {
