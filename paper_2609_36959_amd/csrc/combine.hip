@@ -3,19 +3,15 @@
 // accumulated in fp32 from 0 with one fused multiply-add per slot in slot
 // order; slots whose row is outside [0, T*K) are skipped.
 //
-// fold_kernel: one workgroup per (token, 2 KiB column slice), one wave per
-// slot j (at least two waves). Wave j loads its row's slice (non-temporal,
-// two 16-byte chunks per lane) into LDS; after a barrier two waves fold the
-// K slices in slot order, one 16-byte chunk (eight bf16 values) per thread,
-// and store the slice of y. Each wave has a single row to fetch, so many
-// independent row loads are in flight; on the T=131072, K=8, d=7168
-// workload this runs at 6.5-6.6 TB/s, against 5.6 TB/s for combine_kernel.
-// Four folding waves storing 8 bytes per thread took 3 % longer, and one
-// wave folding two chunks per lane holds the stage longer still.
-//
-// combine_kernel (other shapes): each wave takes one (token, 1 KiB slice)
-// and loads the chunks of all K rows itself, issuing every load before its
-// single store so that no load waits behind a store.
+// fold_kernel: one workgroup per (token, column slice of C KiB), one wave per
+// slot j (at least C waves). Wave j loads its row's slice (non-temporal, C
+// 16-byte chunks per lane) into LDS; after a barrier C waves fold the K
+// slices in slot order, one 16-byte chunk (eight bf16 values) per thread, and
+// store the slice of y. Each wave has a single row to fetch, so many
+// independent row loads are in flight; on the T=131072, K=8, d=7168 workload
+// (C = 2) this runs at 6.5-6.6 TB/s, against 5.6 TB/s when one wave loads the
+// chunks of all K rows. Twice the folding waves, 8 bytes per thread, took 3 %
+// longer, and half as many, two chunks per lane, hold the stage longer still.
 //
 // The node-level combine (the reverse of the node-deduplicated dispatch)
 // follows: node_fold_kernel sums each node's slots into a bf16 partial row
@@ -26,9 +22,6 @@
 
 namespace cobalt {
 namespace {
-
-constexpr int kCombineWaves = 16;
-constexpr int kFoldWaves = 2;  // waves that fold a staged slice (128 chunks, one per thread)
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -44,96 +37,34 @@ __device__ __forceinline__ uint32_t pack_bf16_rne(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// KC = compile-time K (0: any K up to 16, read at run time); with KC the
-// scalar loads of pos and gates are issued back to back before the rows.
-template <bool kF32, int KC>
-__global__ __launch_bounds__(kCombineWaves * 64) void combine_kernel(
-    const u32x4* __restrict__ eo, const int32_t* __restrict__ pos, const float* __restrict__ gates,
-    int64_t T, int Kr, int64_t nch, int64_t TK, u32x4* __restrict__ y, float* __restrict__ y32) {
-    constexpr int KM = KC ? KC : kMaxK;
-    const int K = KC ? KC : Kr;
-    const int64_t groups = (nch + 63) / 64;
-    // wave-uniform item index, so pos and gates come in through scalar loads
-    const int64_t item = (int64_t)blockIdx.x * kCombineWaves +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (item >= T * groups) return;
-    const int64_t t = item / groups;
-    const int64_t c = (item - t * groups) * 64 + (threadIdx.x & 63);
-    int p[KM];
-    float g[KM];
-#pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        p[j] = -1;
-        g[j] = 0.f;
-        if (j < K) {
-            p[j] = pos[t * K + j];
-            g[j] = gates[t * K + j];
-        }
-    }
-    u32x4 v[KM];
-    bool ok[KM];
-#pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        ok[j] = p[j] >= 0 && p[j] < TK && c < nch;
-        if (ok[j]) v[j] = __builtin_nontemporal_load(eo + (int64_t)p[j] * nch + c);
-    }
-    if (c >= nch) return;
-    float acc[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-#pragma unroll
-    for (int j = 0; j < KM; ++j) {
-        if (!ok[j]) continue;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float lo = __uint_as_float(v[j][q] << 16);
-            const float hi = __uint_as_float(v[j][q] & 0xffff0000u);
-            acc[2 * q] = __builtin_fmaf(g[j], lo, acc[2 * q]);
-            acc[2 * q + 1] = __builtin_fmaf(g[j], hi, acc[2 * q + 1]);
-        }
-    }
-    u32x4 out;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        out[q] = pack_bf16_rne(acc[2 * q], acc[2 * q + 1]);
-    __builtin_nontemporal_store(out, y + t * nch + c);
-    if (kF32) {
-        float4* o = (float4*)(y32 + (t * nch + c) * 8);
-        o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        o[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
-    }
-}
-
-// GROUPS = slices of 128 chunks per row, a template parameter so that the
-// block index splits into (token, slice) with a constant division.
-template <bool kF32, int GROUPS>
+template <bool kF32, int C>
 __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     const u32x4* __restrict__ eo, const int32_t* __restrict__ pos, const float* __restrict__ gates,
-    int K, int64_t nch, int64_t TK, u32x4* __restrict__ y, float* __restrict__ y32) {
-    // K slices of 128 chunks (K * 2 KiB, sized at launch): a small stage
+    int K, int64_t nch, int64_t TK, Slices cut, u32x4* __restrict__ y, float* __restrict__ y32) {
+    // K slices of 64 * C chunks (K * C KiB, sized at launch): a small stage
     // lets further workgroups start on a CU once the loading waves of a
     // workgroup have exited, which the wave count alone would not limit
     extern __shared__ u32x4 stage[];
     __shared__ float gate[kMaxK];
     __shared__ int valid[kMaxK];
-    const uint32_t tg = blockIdx.x;
-    const uint32_t t = tg / GROUPS;
-    const uint32_t g = tg - t * GROUPS;
+    uint32_t t, g;
+    cut.split(blockIdx.x, &t, &g);
     const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int64_t c0 = (int64_t)g * 128 + lane;
-    const bool in0 = c0 < nch, in1 = c0 + 64 < nch;
+    const int64_t c0 = (int64_t)g * (64 * C) + lane;
     if (j < K) {
         const int p = pos[(int64_t)t * K + j];
         const bool ok = p >= 0 && p < TK;
-        // both loads are issued before either LDS write: a write right after
-        // its own load would make the second load wait for the first
+        // all loads are issued before any LDS write: a write right after its
+        // own load would make the next load wait for it
         const u32x4* row = eo + (int64_t)(ok ? p : 0) * nch;
-        u32x4 v0, v1;
-        if (ok && in0) v0 = __builtin_nontemporal_load(row + c0);
-        if (ok && in1) v1 = __builtin_nontemporal_load(row + c0 + 64);
-        if (ok && in0) stage[j * 128 + lane] = v0;
-        if (ok && in1) stage[j * 128 + lane + 64] = v1;
+        u32x4 v[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            if (ok && c0 + 64 * i < nch) v[i] = __builtin_nontemporal_load(row + c0 + 64 * i);
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            if (ok && c0 + 64 * i < nch) stage[(j * C + i) * 64 + lane] = v[i];
         const float gj = gates[(int64_t)t * K + j];
         if (lane == 0) {
             valid[j] = ok;
@@ -141,17 +72,17 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
         }
     }
     __syncthreads();
-    // kFoldWaves waves fold: thread i takes chunk i of the slice (eight bf16
-    // values), summing the K slots in slot order, and stores 16 bytes of y
-    if (j >= kFoldWaves) return;
+    // C waves fold: thread i takes chunk i of the slice (eight bf16 values),
+    // summing the K slots in slot order, and stores 16 bytes of y
+    if (j >= C) return;
     const int i = threadIdx.x;
-    const int64_t c = (int64_t)g * 128 + i;
+    const int64_t c = (int64_t)g * (64 * C) + i;
     if (c >= nch) return;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int k = 0; k < K; ++k) {
         if (!valid[k]) continue;
         const float gk = gate[k];
-        const u32x4 v = stage[k * 128 + i];
+        const u32x4 v = stage[k * (64 * C) + i];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             acc[2 * q] = __builtin_fmaf(gk, __uint_as_float(v[q] << 16), acc[2 * q]);
@@ -170,25 +101,6 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     }
 }
 
-template <bool kF32, int GROUPS>
-bool try_fold(const void* eo, const int32_t* pos, const float* gates, int64_t T, int K,
-              int64_t nch, void* y, float* y32, hipStream_t s) {
-    if constexpr (GROUPS == 0) {
-        return false;  // wider rows: combine_kernel
-    } else {
-        if ((nch + 127) / 128 != GROUPS)
-            return try_fold<kF32, GROUPS - 1>(eo, pos, gates, T, K, nch, y, y32, s);
-        const int threads = std::max(K, kFoldWaves) * 64;
-        for_token_ranges(T, (int64_t)GROUPS * threads, [&](int64_t t0, int64_t n) {
-            hipLaunchKernelGGL((fold_kernel<kF32, GROUPS>), dim3((unsigned)(n * GROUPS)),
-                               dim3(threads), (size_t)K * 128 * sizeof(u32x4), s,
-                               (const u32x4*)eo, pos + t0 * K, gates + t0 * K, K, nch, T * K,
-                               (u32x4*)y + t0 * nch, y32 ? y32 + t0 * nch * 8 : nullptr);
-        });
-        return true;
-    }
-}
-
 // Node-level combine: one workgroup per (token, 2 KiB column slice), one wave
 // per slot j (at least two waves). Wave j loads its row's slice like
 // fold_kernel and records its gate and its rank's node; after a barrier two
@@ -201,34 +113,32 @@ bool try_fold(const void* eo, const int32_t* pos, const float* gates, int64_t T,
 // mixed reads and writes). One wave per node row, with the partials summed
 // through LDS after a second barrier, took 4.46 ms; plain instead of
 // non-temporal stores of the partial rows 4.42 ms.
-// GROUPS as for fold_kernel.
-template <int GROUPS>
+template <int C>
 __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
     const u32x4* __restrict__ eo, const int32_t* __restrict__ pos,
     const int32_t* __restrict__ assigned, const float* __restrict__ gates,
     const int32_t* __restrict__ node_pos, int K, int N, int gpn, int64_t nch, int64_t TK,
-    int64_t node_rows, int groups_rt, u32x4* __restrict__ partial, u32x4* __restrict__ y) {
+    int64_t node_rows, Slices cut, u32x4* __restrict__ partial, u32x4* __restrict__ y) {
     extern __shared__ u32x4 stage[];
     __shared__ float gate[kMaxK];
     __shared__ int slot_node[kMaxK];  // node of slot j's rank, -1 for a skipped slot
-    const uint32_t groups = GROUPS ? GROUPS : (uint32_t)groups_rt;
-    const uint32_t tg = blockIdx.x;
-    const uint32_t t = tg / groups;
-    const uint32_t g = tg - t * groups;
+    uint32_t t, g;
+    cut.split(blockIdx.x, &t, &g);
     const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int64_t c0 = (int64_t)g * 128 + lane;
-    const bool in0 = c0 < nch, in1 = c0 + 64 < nch;
+    const int64_t c0 = (int64_t)g * (64 * C) + lane;
     if (j < K) {
         const int p = pos[(int64_t)t * K + j];
         const int r = assigned[(int64_t)t * K + j];
         const bool ok = p >= 0 && p < TK && r >= 0 && r < N * gpn;
         const u32x4* row = eo + (int64_t)(ok ? p : 0) * nch;
-        u32x4 v0, v1;
-        if (ok && in0) v0 = __builtin_nontemporal_load(row + c0);
-        if (ok && in1) v1 = __builtin_nontemporal_load(row + c0 + 64);
-        if (ok && in0) stage[j * 128 + lane] = v0;
-        if (ok && in1) stage[j * 128 + lane + 64] = v1;
+        u32x4 v[C];
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            if (ok && c0 + 64 * i < nch) v[i] = __builtin_nontemporal_load(row + c0 + 64 * i);
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            if (ok && c0 + 64 * i < nch) stage[(j * C + i) * 64 + lane] = v[i];
         const float gj = gates[(int64_t)t * K + j];
         if (lane == 0) {
             gate[j] = gj;
@@ -237,14 +147,14 @@ __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
     }
     // lane n of the folding waves holds the row of (t, n) in partial
     int row = -1;
-    if (j < kFoldWaves && lane < N) {
+    if (j < C && lane < N) {
         const int q = node_pos[(int64_t)t * N + lane];
         row = q >= 0 && q < node_rows ? q : -1;
     }
     __syncthreads();
-    if (j >= kFoldWaves) return;
+    if (j >= C) return;
     const int i = threadIdx.x;
-    const int64_t c = (int64_t)g * 128 + i;
+    const int64_t c = (int64_t)g * (64 * C) + i;
     const int node = lane < K ? slot_node[lane] : -1;  // lane k holds slot k's node and gate
     const int gk = lane < K ? __float_as_int(gate[lane]) : 0;
     float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -254,7 +164,7 @@ __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
         for (uint64_t slots = __ballot(node == n); slots; slots &= slots - 1) {
             const int k = __builtin_ctzll(slots);
             const float gv = __int_as_float(__builtin_amdgcn_readlane(gk, k));
-            const u32x4 v = stage[k * 128 + i];
+            const u32x4 v = stage[k * (64 * C) + i];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 acc[2 * e] = __builtin_fmaf(gv, __uint_as_float(v[e] << 16), acc[2 * e]);
@@ -280,51 +190,24 @@ __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
     __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
 }
 
-template <int GROUPS>
-void launch_node_fold(const void* eo, const int32_t* pos, const int32_t* assigned,
-                      const float* gates, const int32_t* node_pos, int64_t T, int K, int N,
-                      int gpn, int64_t nch, int64_t node_rows, void* partial, void* y,
-                      hipStream_t s) {
-    const int64_t groups = (nch + 127) / 128;
-    if constexpr (GROUPS > 0) {
-        if (groups != GROUPS)
-            return launch_node_fold<GROUPS - 1>(eo, pos, assigned, gates, node_pos, T, K, N, gpn,
-                                                nch, node_rows, partial, y, s);
-    }
-    const int threads = std::max(K, kFoldWaves) * 64;
-    for_token_ranges(T, groups * threads, [&](int64_t t0, int64_t n) {
-        hipLaunchKernelGGL(node_fold_kernel<GROUPS>, dim3((unsigned)(n * groups)), dim3(threads),
-                           (size_t)K * 128 * sizeof(u32x4), s, (const u32x4*)eo, pos + t0 * K,
-                           assigned + t0 * K, gates + t0 * K, node_pos + t0 * N, K, N, gpn, nch,
-                           T * K, node_rows, (int)groups, (u32x4*)partial,
-                           (u32x4*)y + t0 * nch);
-    });
-}
-
 }  // namespace
 
 cobalt_status launch_combine(const void* eo, const int32_t* pos, const float* gates, int64_t T,
                              int K, int64_t d, void* y, float* y32, hipStream_t s) {
     const int64_t nch = d / 8;
-    if (y32 ? try_fold<true, 16>(eo, pos, gates, T, K, nch, y, y32, s)
-            : try_fold<false, 16>(eo, pos, gates, T, K, nch, y, y32, s)) {
-        COBALT_LAUNCH_CHECK();
-        return COBALT_OK;
-    }
-    const int64_t g64 = (nch + 63) / 64;  // one wave per (token, 1 KiB slice)
-    auto launch = [&](auto kernel) {
-        for_token_ranges(T, g64 * 64, [&](int64_t t0, int64_t n) {
-            const int64_t items = n * g64;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)((items + kCombineWaves - 1) / kCombineWaves)),
-                               dim3(kCombineWaves * 64), 0, s, (const u32x4*)eo, pos + t0 * K,
-                               gates + t0 * K, n, K, nch, T * K, (u32x4*)y + t0 * nch,
-                               y32 ? y32 + t0 * nch * 8 : nullptr);
+    by_slices(nch, [&](auto c, const Slices& cut) {
+        constexpr int C = decltype(c)::value;
+        const int threads = std::max(K, C) * 64;
+        for_token_ranges(T, (int64_t)cut.slices * threads, [&](int64_t t0, int64_t n) {
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)(n * cut.slices)), dim3(threads),
+                                   (size_t)K * 64 * C * sizeof(u32x4), s, (const u32x4*)eo,
+                                   pos + t0 * K, gates + t0 * K, K, nch, T * K, cut,
+                                   (u32x4*)y + t0 * nch, y32 ? y32 + t0 * nch * 8 : nullptr);
+            };
+            y32 ? launch(fold_kernel<true, C>) : launch(fold_kernel<false, C>);
         });
-    };
-    if (K == 8)
-        y32 ? launch(combine_kernel<true, 8>) : launch(combine_kernel<false, 8>);
-    else
-        y32 ? launch(combine_kernel<true, 0>) : launch(combine_kernel<false, 0>);
+    });
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;
 }
@@ -335,8 +218,17 @@ cobalt_status launch_node_combine(const void* eo, const int32_t* pos, const int3
                                   hipStream_t s) {
     const int64_t nch = d / 8;
     const int64_t node_rows = T * std::min(K, N);
-    launch_node_fold<16>(eo, pos, assigned, gates, node_pos, T, K, N, gpn, nch, node_rows,
-                         partial, y, s);
+    by_slices(nch, [&](auto c, const Slices& cut) {
+        constexpr int C = decltype(c)::value;
+        const int threads = std::max(K, C) * 64;
+        for_token_ranges(T, (int64_t)cut.slices * threads, [&](int64_t t0, int64_t n) {
+            hipLaunchKernelGGL(node_fold_kernel<C>, dim3((unsigned)(n * cut.slices)), dim3(threads),
+                               (size_t)K * 64 * C * sizeof(u32x4), s, (const u32x4*)eo,
+                               pos + t0 * K, assigned + t0 * K, gates + t0 * K, node_pos + t0 * N,
+                               K, N, gpn, nch, T * K, node_rows, cut, (u32x4*)partial,
+                               (u32x4*)y + t0 * nch);
+        });
+    });
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;
 }

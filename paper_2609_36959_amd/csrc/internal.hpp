@@ -107,6 +107,56 @@ void by_row(int K, const void* p, F&& f) {
         vec(std::integral_constant<int, 16>());
 }
 
+// A row of nch 16-byte chunks in slices of 64 * c chunks, and a workgroup's
+// index b < 2^31 split into (token, slice) without a division:
+// b / slices = (b * magic) >> shift, with shift = 31 + ceil(log2 slices) and
+// magic = ceil(2^shift / slices).
+struct Slices {
+    uint32_t slices, magic, shift;
+    __device__ __forceinline__ void split(uint32_t b, uint32_t* t, uint32_t* g) const {
+        *t = (uint32_t)(((uint64_t)b * magic) >> shift);
+        *g = b - *t * slices;
+    }
+};
+inline Slices cut_row(int64_t nch, int c) {
+    Slices s;
+    s.slices = (uint32_t)((nch + 64 * c - 1) / (64 * c));
+    int lg = 0;
+    while ((1u << lg) < s.slices) ++lg;
+    s.shift = 31 + lg;
+    s.magic = (uint32_t)(((uint64_t(1) << s.shift) + s.slices - 1) / s.slices);
+    return s;
+}
+// Chunks per lane of a wave that moves a slice of a row of nch chunks: two,
+// but one for rows of a single wave's width, and three where a second slice
+// of two would be more than half empty or the row ends early in it. Pack and
+// combine of 16384 tokens, K = 8, in us with one | two | three:
+//   nch  48:  15.3 + 25.3 | 16.6 + 25.7 | 20.7 + 29.7
+//   nch 112:  35.2 + 50.8 | 39.1 + 40.6 | 37.7 + 48.0
+//   nch 144:  46.0 + 70.9 | 60.6 + 69.9 | 48.9 + 63.1
+//   nch 192:  64.8 + 78.4 | 69.3 + 78.4 | 68.0 + 71.1
+//   nch 208:  83.2 + 97.5 | 71.7 + 81.8 | 91.8 + 118
+//   nch 360:   130 + 153  |  133 + 128  |  127 + 139
+// Long rows of one chunk per lane pack faster only while x comes out of the
+// memory-side cache: T = 32768, nch = 512 0.34 against 0.47 ms, but T =
+// 131072, nch = 896 3.8 against 2.9 ms.
+inline int chunks_per_lane(int64_t nch) {
+    return nch <= 64 ? 1 : nch > 128 && nch <= 192 ? 3 : 2;
+}
+
+// Calls f(C, cut) with the row's chunks per lane C and its slices.
+template <typename F>
+void by_slices(int64_t nch, F&& f) {
+    const int c = chunks_per_lane(nch);
+    const Slices cut = cut_row(nch, c);
+    if (c == 1)
+        f(std::integral_constant<int, 1>(), cut);
+    else if (c == 2)
+        f(std::integral_constant<int, 2>(), cut);
+    else
+        f(std::integral_constant<int, 3>(), cut);
+}
+
 struct DeviceLayout {
     int device;
     int32_t N, g, G, E, S;
