@@ -1,8 +1,8 @@
 // Dispatch pack: the row copies behind the layouts of layout.hip.
 //
-//   scatter       per-pair layout: one wave per (token, slice, slot) reads
-//                 the slice of x (from the cache for all but the first of the
-//                 token's K waves) and stores it to the slot's packed row
+//   scatter       per-pair layout: one wave per (token, slice, slot or two)
+//                 reads the slice of x (from the cache for all but the first
+//                 of the token's waves) and stores it to the slots' rows
 //   node_scatter  node-deduplicated layout: four waves per (token, slice)
 //                 with two or four nodes each
 #include <algorithm>
@@ -14,14 +14,14 @@
 namespace cobalt {
 namespace {
 
-// Row scatter for the per-pair layout: one workgroup per (token, slice), one
-// wave per slot j. The K waves that copy one slice of x[t] share a workgroup,
-// so the slice is read from HBM once and from the cache K - 1 times (plain
-// loads keep it cached); each wave then issues a single burst of C KiB to one
-// packed row, with non-temporal stores. On the T=131072, K=8, d=7168 workload
-// this reaches 5.7 TB/s, where one wave that stores its slice to all K rows
-// reaches 5.1.
-template <int C>
+// Row scatter for the per-pair layout: one workgroup per (token, slice of C
+// KiB), R slots per wave (j, j + waves, ...). The waves that copy one slice of
+// x[t] share a workgroup, so the slice is read from HBM once and from the
+// cache by all waves but the first (plain loads keep it cached); each wave
+// then issues a burst of C KiB to each of its packed rows, with non-temporal
+// stores. On the T=131072, K=8, d=7168 workload (C = 2, R = 1) this reaches
+// 5.9 TB/s, where one wave that stores its slice to all K rows reaches 5.1.
+template <int C, int R>
 __global__ __launch_bounds__(kMaxK * 64) void scatter_kernel(
     const u32x4* __restrict__ x, const int32_t* __restrict__ pos, int K, int64_t nch,
     int64_t bound, Slices cut, u32x4* __restrict__ packed) {
@@ -29,7 +29,7 @@ __global__ __launch_bounds__(kMaxK * 64) void scatter_kernel(
     cut.split(blockIdx.x, &t, &g);
     const int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t c0 = (int64_t)g * (64 * C) + (threadIdx.x & 63);
-    // The x loads are issued before the packed row is read: a branch on the
+    // The x loads are issued before the packed rows are read: a branch on the
     // row first would make every wave wait for that load before its own
     // loads start (measured: 3.45 ms instead of 2.95 ms). The in-range
     // guards also keep them there: without them the compiler sinks the
@@ -39,17 +39,49 @@ __global__ __launch_bounds__(kMaxK * 64) void scatter_kernel(
 #pragma unroll
     for (int i = 0; i < C; ++i)
         if (c0 + 64 * i < nch) v[i] = row[c0 + 64 * i];
-    const int p = pos[(int64_t)t * K + j];
-    if (p < 0 || p >= bound) return;
-    // The descriptor of the row's slice drops stores past the row's end, so
-    // the stores need no guard of their own: all issue back to back from one
+    const int waves = blockDim.x >> 6;
+    int p[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int slot = j + waves * k;
+        p[k] = R == 1 || slot < K ? pos[(int64_t)t * K + slot] : -1;
+    }
+    // The descriptor of a row's slice drops stores past the row's end, so the
+    // stores need no guard of their own: all issue back to back from one
     // offset register.
     const int64_t first = (int64_t)g * (64 * C);
-    u32x4* dst = packed + (int64_t)p * nch + first;
     const int32_t bytes = (int32_t)min(nch - first, (int64_t)(64 * C)) * 16;
     const int32_t off = (threadIdx.x & 63) * 16;
 #pragma unroll
-    for (int i = 0; i < C; ++i) store_stream(v[i], dst, bytes, off + 1024 * i);
+    for (int k = 0; k < R; ++k) {
+        if (p[k] < 0 || p[k] >= bound) continue;
+        u32x4* dst = packed + (int64_t)p[k] * nch + first;
+#pragma unroll
+        for (int i = 0; i < C; ++i) store_stream(v[i], dst, bytes, off + 1024 * i);
+    }
+}
+
+// How scatter_kernel moves the rows of a call. Times in us on outputs of 4 to
+// 15 GB with x from HBM, 2 KiB slices and a wave per row | the shape taken:
+//   K <= 2: 1 KiB slices, a wave per row. K = 2, d = 4096: 633 | 497;
+//     d = 2048: 286 | 249; d = 7168: 1035 | 898.
+//   K = 3, 4, 6, 8, 10, 16: 1 KiB slices, two rows per wave. K = 8, d = 4096:
+//     1646 | 1557; d = 8192: 2332 | 2153; K = 6, d = 4096: 1230 | 1188; K =
+//     16, d = 4096: 1722 | 1383; K = 10: 1705 | 1578. With K = 4, 6 or 8 and
+//     an odd number of 2 KiB slices from five on, those walk over all XCDs
+//     and stay ahead (K = 8, d = 7168: 2304 against 2335).
+//   other K (workgroups of an odd number of waves, or three): 2 KiB slices.
+//     K = 5, d = 4096: 1030 against 1107 us; K = 12: 1479 against 1577.
+// Rows that are no whole number of KiB, or short, go by chunks_per_lane.
+struct PackShape {
+    int c, rows;
+};
+PackShape pack_shape(int K, int64_t nch) {
+    const bool whole = nch % 64 == 0 && (nch == 128 || nch >= 256);
+    if (whole && K <= 2 && nch >= 256) return {1, 1};
+    if (whole && (K == 3 || K == 10 || K == 16)) return {1, 2};
+    if (whole && (K == 4 || K == 6 || K == 8) && (nch <= 512 || nch % 256 != 128)) return {1, 2};
+    return {chunks_per_lane(nch), 1};
 }
 
 // Row scatter for the node-deduplicated layout: one workgroup of
@@ -100,12 +132,23 @@ cobalt_status launch_dispatch(const int32_t* assigned, const int32_t* src, int64
         return st;
     if (T == 0 || !x) return COBALT_OK;
     const int64_t nch = d / 8;
-    by_slices(nch, [&](auto c, const Slices& cut) {
-        for_token_ranges(T, (int64_t)cut.slices * K * 64, [&](int64_t t0, int64_t n) {
-            hipLaunchKernelGGL(scatter_kernel<decltype(c)::value>, dim3((unsigned)(n * cut.slices)),
-                               dim3(K * 64), 0, s, (const u32x4*)x + t0 * nch, pos + t0 * K, K,
-                               nch, T * K, cut, (u32x4*)packed);
-        });
+    const PackShape shape = pack_shape(K, nch);
+    const Slices cut = cut_row(nch, shape.c);
+    const int threads = (K + shape.rows - 1) / shape.rows * 64;
+    for_token_ranges(T, (int64_t)cut.slices * threads, [&](int64_t t0, int64_t n) {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(n * cut.slices)), dim3(threads), 0, s,
+                               (const u32x4*)x + t0 * nch, pos + t0 * K, K, nch, T * K, cut,
+                               (u32x4*)packed);
+        };
+        if (shape.rows == 2)
+            launch(scatter_kernel<1, 2>);
+        else if (shape.c == 1)
+            launch(scatter_kernel<1, 1>);
+        else if (shape.c == 2)
+            launch(scatter_kernel<2, 1>);
+        else
+            launch(scatter_kernel<3, 1>);
     });
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;

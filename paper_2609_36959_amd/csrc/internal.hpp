@@ -137,9 +137,9 @@ inline Slices cut_row(int64_t nch, int c) {
 //   nch 192:  64.8 + 78.4 | 69.3 + 78.4 | 68.0 + 71.1
 //   nch 208:  83.2 + 97.5 | 71.7 + 81.8 | 91.8 + 118
 //   nch 360:   130 + 153  |  133 + 128  |  127 + 139
-// Long rows of one chunk per lane pack faster only while x comes out of the
-// memory-side cache: T = 32768, nch = 512 0.34 against 0.47 ms, but T =
-// 131072, nch = 896 3.8 against 2.9 ms.
+// Long rows of one chunk per lane and row pack faster only while x comes out
+// of the memory-side cache: T = 32768, nch = 512 0.34 against 0.47 ms, but T
+// = 131072, nch = 896 3.8 against 2.9 ms.
 inline int chunks_per_lane(int64_t nch) {
     return nch <= 64 ? 1 : nch > 128 && nch <= 192 ? 3 : 2;
 }

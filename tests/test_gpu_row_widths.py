@@ -1,7 +1,7 @@
 """Every call on rows at the edges of the row copies' and folds' slices (one
 chunk per lane up to 64 chunks of 16 bytes, three from 129 to 192, else two),
-with fewer and more slots than folding waves, and rows of many slices, bit for
-bit against the oracle."""
+with fewer and more slots than folding waves, packs of one and two rows per
+wave, and rows of many slices, bit for bit against the oracle."""
 import pytest
 import torch
 
@@ -21,8 +21,8 @@ def gpu():
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("nch", [1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 257, 384, 896, 2049,
-                                 2176])
-@pytest.mark.parametrize("K,N", [(1, 3), (2, 2), (7, 3), (16, 9)])
+@pytest.mark.parametrize("nch", [1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 256, 257, 384, 512,
+                                 640, 896, 2049, 2176])
+@pytest.mark.parametrize("K,N", [(1, 3), (2, 2), (3, 2), (7, 3), (8, 3), (16, 9)])
 def test_row_width(nch, K, N):
     shapes.test_random_shape(N, 2, 18 if N != 2 else 20, 18, K, 37, 8 * nch, "ragged", nch + K)
