@@ -403,7 +403,8 @@ __global__ __launch_bounds__(kThreads) void any_count_kernel(
     __shared__ uint32_t window[kWindow];
     __shared__ uint32_t h[kMaxG];
     const int64_t p0 = blockIdx.x * tile, p1 = min(p0 + tile, TK);
-    const int lo = src[p0 / K], rows = window_rows(lo, src[(p1 - 1) / K], G, G);
+    const int first = src[p0 / K], rows = window_rows(first, src[(p1 - 1) / K], G, G);
+    const int lo = rows ? first : 0;
     for (int i = threadIdx.x; i < rows * G; i += kThreads) window[i] = 0;
     for (int r = threadIdx.x; r < G; r += kThreads) h[r] = 0;
     __syncthreads();
@@ -770,7 +771,8 @@ __global__ __launch_bounds__(kThreads) void any_node_count_kernel(
     __shared__ uint32_t h[kMaxN];
     const int G = N * g;
     const int64_t t0 = blockIdx.x * tile, t1 = min(t0 + tile, T);
-    const int lo = src[t0], rows = window_rows(lo, src[t1 - 1], G, N);
+    const int first = src[t0], rows = window_rows(first, src[t1 - 1], G, N);
+    const int lo = rows ? first : 0;
     for (int i = threadIdx.x; i < rows * N; i += kThreads) window[i] = 0;
     if (threadIdx.x < kMaxN) h[threadIdx.x] = 0;
     __syncthreads();
