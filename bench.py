@@ -29,8 +29,10 @@ sys.path.insert(0, ROOT)
 HBM_PEAK = 8.0e12  # MI355X HBM3E, bytes/s
 METRIC = "routed tokens/sec (stats+assign+pack+combine), % of HBM peak, 1 MI355X"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_{call}_{workload}.txt")
-KERNEL_SOURCES = {"cobalt_dispatch_pack": "dispatch.hip", "cobalt_combine": "combine.hip",
-                  "cobalt_node_dispatch_pack": "dispatch.hip", "cobalt_node_combine": "combine.hip"}
+KERNEL_SOURCES = {"cobalt_dispatch_pack": ("dispatch.hip", "layout.hip"),
+                  "cobalt_combine": ("combine.hip",),
+                  "cobalt_node_dispatch_pack": ("dispatch.hip", "layout.hip"),
+                  "cobalt_node_combine": ("combine.hip",)}
 
 
 def parse():
@@ -78,17 +80,19 @@ def node_dispatch_bytes(w, rows):
 
 
 def node_combine_bytes(w, rows):
-    """Bytes the node-level combine must move: the node side reads every
-    pair's expert row, its pos, rank and gate and the node rows, and writes
-    `rows` bf16 partials; the source side reads the partials and node_pos
-    and writes y."""
+    """Bytes the node-level combine must move: it reads every pair's expert
+    row, its pos, rank and gate and the node rows, and writes `rows` bf16
+    partials and y (the partials are summed into y where they are made)."""
     T, K, d, N = w.T, w.K, w.d, w.N
-    return T * K * d * 2 + T * K * 12 + 2 * T * N * 4 + 2 * rows * d * 2 + T * d * 2
+    return T * K * d * 2 + T * K * 12 + T * N * 4 + rows * d * 2 + T * d * 2
 
 
 def source_digest(call):
-    p = os.path.join(ROOT, "paper_2609_36959_amd", "csrc", KERNEL_SOURCES[call])
-    return hashlib.sha256(open(p, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in KERNEL_SOURCES[call]:
+        with open(os.path.join(ROOT, "paper_2609_36959_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(call, workload):
