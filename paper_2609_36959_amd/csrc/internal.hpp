@@ -52,7 +52,7 @@ __device__ __forceinline__ void store_through(const u32x4& v, void* base, int32_
 // from an integer, and the product is off by less than x / y * 2^-22.
 struct SmallDiv {
     float inv;
-    __device__ __forceinline__ int operator()(int x) const { return (int)(((float)x + 0.5f) * inv); }
+    __host__ __device__ int operator()(int x) const { return (int)(((float)x + 0.5f) * inv); }
 };
 __host__ __device__ inline SmallDiv divide_by(int64_t v) { return {1.0f / (float)v}; }
 
@@ -113,7 +113,7 @@ void by_row(int K, const void* p, F&& f) {
 // magic = ceil(2^shift / slices).
 struct Slices {
     uint32_t slices, magic, shift;
-    __device__ __forceinline__ void split(uint32_t b, uint32_t* t, uint32_t* g) const {
+    __host__ __device__ void split(uint32_t b, uint32_t* t, uint32_t* g) const {
         *t = (uint32_t)(((uint64_t)b * magic) >> shift);
         *g = b - *t * slices;
     }
