@@ -100,10 +100,12 @@ cobalt_status cobalt_layout_tables(cobalt_layout_t layout, uint32_t* host_node_m
  *   tokens, at most 128 chunks; 2 bytes per bin where a chunk's bins cannot
  *   pass 65535, else 4), 256-byte aligned, owned by the caller; contents on
  *   entry are ignored; it must not be shared by calls that may overlap. The
- *   call updates coact and expert_count with plain (non-atomic) adds, or with
- *   integer atomic adds when it is small and on the diagonal, so calls that
- *   may overlap must not share them either. The counts are exact either way
- *   and do not depend on scheduling.
+ *   size does not fall as T or K grows: one workspace of the size for the
+ *   largest call serves every smaller one with the same E. The call updates
+ *   coact and expert_count with plain (non-atomic) adds, or with integer
+ *   atomic adds when it is small and on the diagonal, so calls that may
+ *   overlap must not share them either. The counts are exact either way and
+ *   do not depend on scheduling.
  * ---------------------------------------------------------------------- */
 size_t cobalt_coact_stats_workspace_bytes(int64_t T, int32_t K, int32_t E);
 

@@ -53,10 +53,11 @@
 //
 // Chunks. A workgroup's LDS atomics queue on its CU, so chunks are short
 // until the partials they add cost as much: 512 tokens (256 up to kDirectE),
-// at most 128 chunks, and with many bands at most kMaxGroups workgroups:
-// E = 1024, 131072 tokens take 56 us with 33 chunks (the uint16 bound) of 16
-// bands against 101 with 128; E = 256, 4096 tokens 14.0 us in 8 chunks
-// against 16.8 in 4.
+// at most 128 chunks, and with many bands at most kMaxGroups workgroups, or
+// twice as many where that keeps the bins uint16 in no more space. E = 1024,
+// 131072 tokens, K = 8 in 16 bands take 55.9 us with 16 chunks of uint32
+// bins, 70 with the 33 that make them uint16, 101 with 128; E = 256, 4096
+// tokens 14.0 us in 8 chunks against 16.8 in 4.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -74,7 +75,6 @@ constexpr int kReduceThreads = 256;
 constexpr int kMaxLgBands = 12;
 constexpr int64_t kTokensPerChunk = 512;
 constexpr int64_t kMaxChunks = 128;
-constexpr int64_t kMaxChunks16 = 128;  // more chunks allowed to keep uint16 partials
 constexpr int kParBands = 2;            // bands for parallelism on large calls
 constexpr int64_t kParPairs = 1 << 18;  // T*K from which bands are used for parallelism
 constexpr int64_t kMaxGroups = 256;
@@ -134,26 +134,37 @@ bool make_plan(int64_t T, int64_t K, int E, int lds_bytes, Plan* p) {
                                                                             : kTokensPerChunk)));
     p->tok_per_chunk = std::max<int64_t>(1, (T + p->nchunks - 1) / p->nchunks);
     // A token adds at most floor(K/2) * ceil(K/2) to one bin (two experts,
-    // each repeated), so a chunk's bins fit in uint16 when its tokens times
-    // that product stay within 65535. More chunks are used to get there when
-    // at most kMaxChunks16 suffice.
+    // each repeated), so chunks of up to 65535 / that product tokens have
+    // uint16 bins. Where the chunks above are longer, more of them are used,
+    // if that takes no more space than these in uint32: the workspace then
+    // never shrinks as T or K grows, and one of the size for a program's
+    // largest call serves its smaller ones (without the bound on space, E =
+    // 1024, K = 8 asked for 142 MB at 520000 tokens, 34 MB at 540000), and
+    // many bands are no slower for it: E = 1024, 262144 tokens 72.6 us
+    // against 105.7 in 65 uint16 chunks, E = 4096, 131072 277 against 657.
+    const int nb = 1 << lgb;
+    p->band_stride = hist_words(E, nb);
+    const auto part = [&](int64_t chunks, int bytes) {
+        return align256((size_t)chunks * nb * p->band_stride * bytes);
+    };
+    const auto counts = [&](int64_t chunks) { return align256((size_t)chunks * E * 4); };
     const int64_t maxpair = (K / 2) * ((K + 1) / 2);
-    p->u16 = p->tok_per_chunk * maxpair <= 65535;
+    const int64_t tok16 = maxpair ? 65535 / maxpair : T + 1;
+    p->u16 = p->tok_per_chunk <= tok16;
     if (!p->u16) {
-        const int64_t n16 = (T * maxpair + 65534) / 65535;
-        if (n16 <= kMaxChunks16) {
+        const int64_t n16 = (T + tok16 - 1) / tok16;
+        if (n16 <= kMaxChunks &&
+            part(n16, 2) + counts(n16) <= part(p->nchunks, 4) + counts(p->nchunks)) {
             p->nchunks = (int)n16;
             p->tok_per_chunk = (T + n16 - 1) / n16;
-            p->u16 = p->tok_per_chunk * maxpair <= 65535;
+            p->u16 = true;
         }
     }
     p->lgb = lgb;
-    const int nb = 1 << lgb;
-    p->band_stride = hist_words(E, nb);
     p->cnt_off = (int32_t)p->band_stride;
     p->lds_bytes = (size_t)(p->band_stride + 2 * cnt_words(E, nb)) * 4;
-    p->part_bytes = align256((size_t)p->nchunks * nb * p->band_stride * (p->u16 ? 2 : 4));
-    p->count_bytes = align256((size_t)p->nchunks * E * 4);
+    p->part_bytes = part(p->nchunks, p->u16 ? 2 : 4);
+    p->count_bytes = counts(p->nchunks);
     return true;
 }
 

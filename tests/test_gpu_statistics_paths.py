@@ -1,9 +1,10 @@
 """The statistics at the edges of their dispatch, against A^T A of the tokens'
 multiplicity matrix: the last call whose workgroups add to coact directly and
 the first with a reduce (by chunks and by E), few and many chunks, the cap on
-workgroups with many bands, every width of the id loads (K and address), K
-that fills the registers and K that does not; a few tokens repeat an id or
-hold one out of range."""
+workgroups with many bands (and where it gives way, so that the bins are
+uint16), every width of the id loads (K and address), K that fills the
+registers and K that does not; a few tokens repeat an id or hold one out of
+range."""
 import numpy as np
 import pytest
 import torch
@@ -31,7 +32,10 @@ def gpu():
     (3000, 40, 12, 0), (3000, 40, 16, 4), (1500, 60, 13, 0), (2000, 50, 10, 2),
     (16895, 200, 8, 0), (17000, 200, 8, 0),  # 32 and 33 chunks of 512: lanes of the reduce
     (131072, 300, 4, 0),
-    (70000, 1024, 8, 0),                    # 16 bands: chunks capped at 16
+    (20000, 1024, 8, 0),                    # 16 bands: chunks capped at 16
+    (70000, 1024, 8, 0),                    # 18 chunks, so that the bins are uint16
+    (140001, 1024, 8, 0),                   # 16 chunks of uint32 bins
+    (140000, 1024, 16, 0),
     (4096, 1500, 6, 0),
 ])
 def test_statistics(T, E, K, shift):
