@@ -294,8 +294,9 @@ cobalt_status cobalt_node_combine(const void* expert_out, const int32_t* pos,
  * Nothing is zeroed (counts accumulate). workspace: device scratch of at
  * least cobalt_replica_load_workspace_bytes(T, K, E, G) bytes, 256-byte
  * aligned, owned by the caller, contents ignored, not shared by calls that
- * may overlap; load is updated with plain adds, so overlapping calls must
- * not share it either.
+ * may overlap; the size does not fall as T, K, E or G grows, so one for the
+ * largest call serves the smaller ones. load is updated with plain adds, so
+ * overlapping calls must not share it either.
  * ---------------------------------------------------------------------- */
 size_t cobalt_replica_load_workspace_bytes(int64_t T, int32_t K, int32_t E, int32_t G);
 

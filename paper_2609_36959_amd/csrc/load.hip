@@ -9,8 +9,8 @@
 //           rows when E*G fits and the grid is large enough without bands).
 //           Pairs come four at a time with 16-byte loads of topk_idx and
 //           assigned_rank where both are aligned. The band's bins are then
-//           written out as uint16 where a chunk's pair count fits, else as
-//           uint32.
+//           written out, at their place among the chunk's E*G bins, as uint16
+//           where a chunk's pair count fits, else as uint32.
 //   reduce  sixteen lanes per group of eight bins sum the chunks (one
 //           16-byte load of eight uint16 bins per chunk), add pairwise
 //           across lanes k and k + 8, exchange halves in three shuffle
@@ -35,11 +35,16 @@ constexpr int64_t kBandWords = 16384;  // 64 KiB of LDS
 // until there were 256 workgroups).
 constexpr int kMinGroups = 256;
 
+// The partials take nchunks * E*G bins however they are cut into bands, so
+// the workspace never shrinks as T, K, E or G grows: one of the size for a
+// program's largest call serves its smaller ones. (With a slot of its own for
+// every band, rounded up, E = 64, G = 32, K = 8 asked for 125440 bytes at T =
+// 58000 and 118784 at T = 60000.)
 struct LoadPlan {
     int nchunks, nbands, band_rows;
     bool u16;                // partial bins stored as uint16
     int64_t pairs_per_chunk; // a multiple of 4
-    int64_t stride;          // bins of one (chunk, band) partial, a multiple of 8
+    int64_t stride;          // bins of a chunk: E*G rounded up to a multiple of 8
     size_t bytes;
 };
 
@@ -48,15 +53,17 @@ LoadPlan make_plan(int64_t T, int K, int E, int G) {
     const int64_t pairs = T * K;
     p.nchunks = (int)std::min<int64_t>(kMaxChunks, std::max<int64_t>(1, pairs / kPairsPerChunk));
     p.pairs_per_chunk = std::max<int64_t>(4, ((pairs + p.nchunks - 1) / p.nchunks + 3) & ~3);
-    // as many bands of equal rows as the LDS needs, or as fill the chip
-    const int64_t fit = std::max<int64_t>(1, std::min<int64_t>(E, kBandWords / G));
+    // as many bands of equal rows as the LDS needs, or as fill the chip; a
+    // band starts at a multiple of eight bins, for its 16-byte stores
+    const int64_t unit = G % 8 == 0 ? 1 : G % 4 == 0 ? 2 : G % 2 == 0 ? 4 : 8;
+    const int64_t fit = kBandWords / G / unit * unit;
     const int64_t fill = std::min<int64_t>(E, (kMinGroups + p.nchunks - 1) / p.nchunks);
     const int64_t bands = std::max((E + fit - 1) / fit, fill);
-    p.band_rows = (int)((E + bands - 1) / bands);
+    p.band_rows = (int)(((E + bands - 1) / bands + unit - 1) / unit * unit);
     p.nbands = (E + p.band_rows - 1) / p.band_rows;
     p.u16 = p.pairs_per_chunk <= 65535;
-    p.stride = ((int64_t)p.band_rows * G + 7) & ~int64_t(7);
-    p.bytes = ((size_t)p.nchunks * p.nbands * p.stride * (p.u16 ? 2 : 4) + 255) & ~size_t(255);
+    p.stride = ((int64_t)E * G + 7) & ~int64_t(7);
+    p.bytes = ((size_t)p.nchunks * p.stride * (p.u16 ? 2 : 4) + 255) & ~size_t(255);
     return p;
 }
 
@@ -72,7 +79,8 @@ __global__ __launch_bounds__(kLoadThreads) void load_count_kernel(
     const int band = blockIdx.x / nchunks;
     const int e_lo = band * band_rows;
     const int e_hi = min(E, e_lo + band_rows);
-    for (int b = threadIdx.x; b < stride; b += kLoadThreads) hist[b] = 0;
+    const int groups = ((e_hi - e_lo) * G + 7) / 8;  // of eight bins, band_rows * G / 8 at most
+    for (int b = threadIdx.x; b < groups * 8; b += kLoadThreads) hist[b] = 0;
     __syncthreads();
     const int64_t p0 = (int64_t)chunk * pairs_per_chunk;
     const int64_t p1 = min(TK, p0 + pairs_per_chunk);
@@ -94,42 +102,36 @@ __global__ __launch_bounds__(kLoadThreads) void load_count_kernel(
     }
     __syncthreads();
     // bins past the band's rows are zero (cleared above, never counted)
-    const int64_t at = (int64_t)blockIdx.x * stride;
-    for (int g = threadIdx.x; g < stride / 8; g += kLoadThreads) {
+    const int64_t at = chunk * stride + (int64_t)e_lo * G;
+    for (int g = threadIdx.x; g < groups; g += kLoadThreads) {
         const u32x4 lo = *reinterpret_cast<const u32x4*>(hist + g * 8);
         const u32x4 hi = *reinterpret_cast<const u32x4*>(hist + g * 8 + 4);
         if constexpr (U16) {
             const u32x4 packed = {lo.x | (lo.y << 16), lo.z | (lo.w << 16), hi.x | (hi.y << 16),
                                   hi.z | (hi.w << 16)};
-            store_through(packed, static_cast<uint16_t*>(part) + at, (int32_t)stride * 2, g * 16);
+            store_through(packed, static_cast<uint16_t*>(part) + at, groups * 16, g * 16);
         } else {
             uint32_t* out = static_cast<uint32_t*>(part) + at;
-            store_through(lo, out, (int32_t)stride * 4, g * 32);
-            store_through(hi, out, (int32_t)stride * 4, g * 32 + 16);
+            store_through(lo, out, groups * 32, g * 32);
+            store_through(hi, out, groups * 32, g * 32 + 16);
         }
     }
 }
 
 template <bool U16>
 __global__ __launch_bounds__(kReduceThreads) void load_reduce_kernel(
-    const void* __restrict__ part, int E, int G, int nchunks, int band_rows, int64_t stride,
+    const void* __restrict__ part, int64_t bins, int nchunks, int64_t stride,
     uint32_t* __restrict__ load) {
-    const int64_t groups = stride / 8;
     const int64_t gid = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x;
-    const int64_t item = gid / kReduceLanes;
     const int k = (int)(gid % kReduceLanes);
-    const int band = (int)(item / groups);
-    if (band >= (E + band_rows - 1) / band_rows) return;  // whole groups of lanes
-    const int64_t w0 = (item % groups) * 8;
-    const int64_t band_bins = (int64_t)(min(E, (band + 1) * band_rows) - band * band_rows) * G;
-    const int64_t w = w0 + (k & 7);
-    const int64_t bin = (int64_t)band * band_rows * G + w;
-    const bool real = k < 8 && w < band_bins;
+    const int64_t w0 = gid / kReduceLanes * 8;
+    if (w0 >= bins) return;  // whole groups of lanes
+    const int64_t bin = w0 + (k & 7);
+    const bool real = k < 8 && bin < bins;
     const uint32_t prev = real ? load[bin] : 0u;
     uint32_t s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int64_t base = (int64_t)band * nchunks * stride + w0;
     if constexpr (U16) {
-        const uint16_t* src = static_cast<const uint16_t*>(part) + base;
+        const uint16_t* src = static_cast<const uint16_t*>(part) + w0;
 #pragma unroll 4
         for (int c = k; c < nchunks; c += kReduceLanes) {
             const u32x4 v = *reinterpret_cast<const u32x4*>(src + (int64_t)c * stride);
@@ -140,7 +142,7 @@ __global__ __launch_bounds__(kReduceThreads) void load_reduce_kernel(
             }
         }
     } else {
-        const uint32_t* src = static_cast<const uint32_t*>(part) + base;
+        const uint32_t* src = static_cast<const uint32_t*>(part) + w0;
 #pragma unroll 4
         for (int c = k; c < nchunks; c += kReduceLanes) {
             const u32x4* q = reinterpret_cast<const u32x4*>(src + (int64_t)c * stride);
@@ -200,14 +202,14 @@ cobalt_status launch_replica_load(const int32_t* topk, const int32_t* assigned, 
     else
         vec ? count(load_count_kernel<true, false>) : count(load_count_kernel<false, false>);
     COBALT_LAUNCH_CHECK();
-    const int64_t items = (int64_t)p.nbands * (p.stride / 8) * kReduceLanes;
+    const int64_t items = p.stride / 8 * kReduceLanes;
     const dim3 grid((unsigned)((items + kReduceThreads - 1) / kReduceThreads));
     if (p.u16)
-        hipLaunchKernelGGL(load_reduce_kernel<true>, grid, dim3(kReduceThreads), 0, s, ws, E, G,
-                           p.nchunks, p.band_rows, p.stride, load);
+        hipLaunchKernelGGL(load_reduce_kernel<true>, grid, dim3(kReduceThreads), 0, s, ws,
+                           (int64_t)E * G, p.nchunks, p.stride, load);
     else
-        hipLaunchKernelGGL(load_reduce_kernel<false>, grid, dim3(kReduceThreads), 0, s, ws, E, G,
-                           p.nchunks, p.band_rows, p.stride, load);
+        hipLaunchKernelGGL(load_reduce_kernel<false>, grid, dim3(kReduceThreads), 0, s, ws,
+                           (int64_t)E * G, p.nchunks, p.stride, load);
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;
 }
