@@ -28,7 +28,11 @@
 //     to 9.8 against 8.2; 1024 tokens 6 to 10 us against 7.2 to 8, 2048 7 to
 //     15 against 7.3. Sources given: 24576 pairs 10.5 to 12.2 us against 14
 //     to 17, 49152 15.4 to 19.5 against 14.1 to 17; 4096 tokens 8.6 to 17.6
-//     against 11 to 16.7, 8192 12 to 19 against 12 to 16.4.
+//     against 11 to 16.7, 8192 12 to 19 against 12 to 16.4. With few ranks
+//     the pairs' LDS atomics queue on few words, in every workgroup for all
+//     pairs, and the limit is lower (small_pairs): 24576 pairs on 1, 2, 3, 4,
+//     6 and 8 ranks take 26.2, 21.0, 17.4, 15.6, 14.0 and 12.4 us against
+//     11.6, 14.1, 13.7, 13.3, 13.3 and 13.2.
 #include <algorithm>
 #include <type_traits>
 
@@ -418,13 +422,18 @@ __global__ __launch_bounds__(kThreads) void any_count_kernel(
         }
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) {
+            uint32_t n = 1;
+            if (G == 1) {  // one bucket: the wave adds once (11.6 us for 32768 pairs, not 14.6)
+                n = (uint32_t)__popcll(__ballot(b[c] >= 0));
+                b[c] = (threadIdx.x & 63) == 0 && n ? 0 : -1;
+            }
             if (b[c] < 0) continue;
             const int w = b[c] - lo * G;
             if (w >= 0 && w < rows * G) {
-                atomicAdd(&window[w], 1u);
+                atomicAdd(&window[w], n);
             } else {
-                atomicAdd(&counts[b[c]], 1);
-                atomicAdd(&h[b[c] % G], 1u);
+                atomicAdd(&counts[b[c]], (int32_t)n);
+                atomicAdd(&h[b[c] % G], n);
             }
         }
     }
@@ -937,6 +946,15 @@ size_t node_dispatch_workspace_bytes(int64_t T, int N, int G) {
     return workspace_bytes(T, kTokensPerWord, G, N);
 }
 
+// Most pairs of a call on whole-call workgroups. With source ranks given the
+// line lies about where the other scheme is as fast: at 8200 pairs for one
+// rank, 13900, 16600, 19500, 21400 and 22800 for 2 to 6, 26700 for 8, and
+// past kSmallPairsAny from 16 on.
+static int64_t small_pairs(bool src, int G) {
+    if (!src || G == 1) return kSmallPairs;
+    return std::min<int64_t>(kSmallPairsAny, kSmallPairs + 2304 * (int64_t)G);
+}
+
 // Clears counts[R][C] in a kernel: a recorded memset node is no part of a
 // captured call.
 static void launch_clear(int32_t* counts, int n, hipStream_t s) {
@@ -960,7 +978,7 @@ cobalt_status launch_layout(const int32_t* assigned, const int32_t* src, int64_t
     if (T == 0) {
         launch_clear(counts, G * G, s);
         launch_scan(counts, G, G, offsets, base, s);
-    } else if (G <= kSmallG && TK <= (src ? kSmallPairsAny : kSmallPairs)) {
+    } else if (G <= kSmallG && TK <= small_pairs(src != nullptr, G)) {
         const unsigned blocks = (unsigned)((TK + kThreads - 1) / kThreads);
         hipLaunchKernelGGL(small_layout_kernel, dim3(blocks), dim3(kThreads), 0, s, assigned, src,
                            (int)TK, G, divide_by(K), divide_by(src ? 1 : TK / G), counts, offsets,

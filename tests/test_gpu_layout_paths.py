@@ -1,7 +1,7 @@
 """The layouts of both dispatches at the edges of the layout kernels' ranges,
 against a stable sort in numpy: whole-call workgroups up to their pair limits
-(8192, or 32768 with source ranks given; 1024 and 4096 tokens for the node
-rows) and beyond, per-source tiles of 4096 pairs (512 tokens) with one pair too
+(8192, or up to 32768, by the number of ranks, with source ranks given; 1024
+and 4096 tokens for the node rows) and beyond, per-source tiles of 4096 pairs (512 tokens) with one pair too
 many, tiles of several passes (past 1024 tiles, or 256 with source ranks
 given), windows over the sources that do not fit, G up to 64 and above, ids at
 addresses that allow only 4- or 8-byte reads, and workspaces of exactly the
@@ -52,6 +52,13 @@ CASES = [
     (4096, 8, 8, 8, "any", 0),           # 32768 pairs, 4096 tokens: the limits with sources
     (4097, 8, 8, 8, "any", 4),
     (4097, 8, 8, 8, "one", 0),
+    (8192, 1, 1, 1, "any", 0),           # 8192 pairs: the limit for one rank
+    (8193, 1, 1, 1, "any", 0),
+    (70001, 3, 1, 1, "any", 1),          # one rank, several tiles
+    (2133, 6, 2, 1, "any", 0),           # 12798 and 12804 pairs, two ranks: 12800
+    (2134, 6, 1, 2, "any", 1),
+    (3328, 8, 2, 4, "any", 0),           # 26624 pairs: the limit for eight ranks
+    (3329, 8, 2, 4, "one", 0),
     (8192, 1, 4, 2, "null", 0),
     (1040, 16, 13, 5, "null", 0),        # G = 65: no whole-call workgroups
     (1025, 16, 13, 5, "any", 0),         # first rows from the scan kernel
