@@ -61,27 +61,60 @@ __global__ __launch_bounds__(kMaxK * 64) void scatter_kernel(
     }
 }
 
-// How scatter_kernel moves the rows of a call. Times in us on outputs of 4 to
-// 15 GB with x from HBM, 2 KiB slices and a wave per row | the shape taken:
-//   K <= 2: 1 KiB slices, a wave per row. K = 2, d = 4096: 633 | 497;
-//     d = 2048: 286 | 249; d = 7168: 1035 | 898.
-//   K = 3, 4, 6, 8, 10, 16: 1 KiB slices, two rows per wave. K = 8, d = 4096:
-//     1646 | 1557; d = 8192: 2332 | 2153; K = 6, d = 4096: 1230 | 1188; K =
-//     16, d = 4096: 1722 | 1383; K = 10: 1705 | 1578. With K = 4, 6 or 8 and
-//     an odd number of 2 KiB slices from five on, those walk over all XCDs
-//     and stay ahead (K = 8, d = 7168: 2304 against 2335).
-//   other K (workgroups of an odd number of waves, or three): 2 KiB slices.
-//     K = 5, d = 4096: 1030 against 1107 us; K = 12: 1479 against 1577.
+// How scatter_kernel moves the rows of a call: 2 KiB slices and a wave per
+// row, or a shape of 1 KiB slices where the output is larger than the
+// memory-side cache (with less the shapes are level, and K = 1 takes 14 %
+// longer in 1 KiB slices below 32 MB). Past that, what is fastest depends on
+// how the rows' addresses fall on the memory channels, that is on K, d and
+// the routing together, so the shapes are a table of what holds over 14600
+// calls (all K; d from 1024 to 8192; T from 2048 to 131072; 8 to 64 ranks;
+// uniform and skewed routing, half of it from the assignment), as the
+// geometric mean (and the largest) of the ratio to the time in 2 KiB slices,
+// for rows of whole KiB from d = 2048 on:
+//   1 KiB slices, a wave per row: K = 1 0.91 (1.07), K = 2 0.91 (1.09).
+//   1 KiB slices, two rows per wave: K = 3 0.94 (1.06), K = 10 0.92 (1.05),
+//     K = 16 0.90 (1.18) for whole 2 KiB (1.03 (1.08) at d = 2560), K = 6
+//     0.96 (1.07) and K = 8 0.94 (1.18) where d is a power of two (K = 6 1.00
+//     (1.08) else).
+//     K = 8 has buckets to avoid: sources in equal blocks whose buckets, if
+//     they are equal too, lie at multiples of a power of two of at least 8
+//     MiB, so that all ranks' rows meet the same channels at a time: 0.97
+//     (1.42), worst with uniform routing (T = 65536, d = 4096, 16 ranks: 830
+//     us in 2 KiB slices, 1177 in two rows per wave).
+//     Not taken: K = 4 0.99 (1.28), 5 1.01 (1.10), 7 1.00 (1.06), 9 1.07
+//     (1.26), 11 1.02 (1.12), 12 0.98 (1.05), 13 0.98 (1.10), 14 0.97 (1.07)
+//     and 15 0.94 (1.09).
 // Rows that are no whole number of KiB, or short, go by chunks_per_lane.
 struct PackShape {
     int c, rows;
 };
-PackShape pack_shape(int K, int64_t nch) {
-    const bool whole = nch % 64 == 0 && (nch == 128 || nch >= 256);
-    if (whole && K <= 2 && nch >= 256) return {1, 1};
-    if (whole && (K == 3 || K == 10 || K == 16)) return {1, 2};
-    if (whole && (K == 4 || K == 6 || K == 8) && (nch <= 512 || nch % 256 != 128)) return {1, 2};
-    return {chunks_per_lane(nch), 1};
+constexpr int64_t kCachedBytes = 256 << 20;
+
+PackShape pack_shape(int64_t T, int K, int G, bool equal_blocks, int64_t nch) {
+    const PackShape plain = {chunks_per_lane(nch), 1};
+    const int64_t bytes = T * K * nch * 16;
+    if (nch % 64 != 0 || nch < 256 || bytes <= kCachedBytes) return plain;
+    const auto power_of_two = [](int64_t v) { return (v & (v - 1)) == 0; };
+    const int64_t ranks2 = (int64_t)G * G;
+    switch (K) {
+        case 1:
+        case 2:
+            return {1, 1};
+        case 3:
+        case 10:
+            return {1, 2};
+        case 6:
+            return power_of_two(nch) ? PackShape{1, 2} : plain;
+        case 8:
+            if (equal_blocks && bytes % ranks2 == 0 && power_of_two(bytes / ranks2) &&
+                bytes / ranks2 >= (8 << 20))
+                return plain;
+            return power_of_two(nch) ? PackShape{1, 2} : plain;
+        case 16:
+            return nch % 128 == 0 ? PackShape{1, 2} : plain;
+        default:
+            return plain;
+    }
 }
 
 // Row scatter for the node-deduplicated layout: one workgroup of
@@ -132,7 +165,7 @@ cobalt_status launch_dispatch(const int32_t* assigned, const int32_t* src, int64
         return st;
     if (T == 0 || !x) return COBALT_OK;
     const int64_t nch = d / 8;
-    const PackShape shape = pack_shape(K, nch);
+    const PackShape shape = pack_shape(T, K, G, src == nullptr, nch);
     const Slices cut = cut_row(nch, shape.c);
     const int threads = (K + shape.rows - 1) / shape.rows * 64;
     for_token_ranges(T, (int64_t)cut.slices * threads, [&](int64_t t0, int64_t n) {

@@ -1,7 +1,9 @@
 """Every call on rows at the edges of the row copies' and folds' slices (one
 chunk per lane up to 64 chunks of 16 bytes, three from 129 to 192, else two),
-with fewer and more slots than folding waves, packs of one and two rows per
-wave, and rows of many slices, bit for bit against the oracle."""
+with fewer and more slots than folding waves, and rows of many slices, bit for
+bit against the oracle; and packs larger than the memory-side cache, which
+move the rows in shapes of their own."""
+import numpy as np
 import pytest
 import torch
 
@@ -26,3 +28,37 @@ def gpu():
 @pytest.mark.parametrize("K,N", [(1, 3), (2, 2), (3, 2), (7, 3), (8, 3), (16, 9)])
 def test_row_width(nch, K, N):
     shapes.test_random_shape(N, 2, 18 if N != 2 else 20, 18, K, 37, 8 * nch, "ragged", nch + K)
+
+
+# outputs of more than 256 MiB: every K with 1 KiB slices (two rows per wave
+# from K = 3), rows of an odd number of KiB, of no power of two, of no whole
+# KiB; equal blocks of sources with buckets of 16 MiB, and sources given
+@pytest.mark.parametrize("K,d", [(1, 2048), (2, 2560), (3, 2048), (3, 2560), (6, 2048), (6, 3072),
+                                 (8, 4096), (10, 2560), (16, 2048), (16, 2560), (8, 2056)])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_large_pack(K, d, ragged):
+    G = 8
+    T = 1 << 14 if (K, d) == (8, 4096) else ((1 << 28) // (K * d * 2) // G + 3) * G
+    print(f"large pack T={T} K={K} d={d} ragged={ragged}", flush=True)
+    rng = np.random.default_rng(K + d)
+    a = rng.integers(0, G, (T, K)).astype(np.int32)
+    if ragged:
+        a[rng.random((T, K)) < 0.01] = -1    # skipped slots
+    a = torch.from_numpy(a).cuda()
+    src = torch.from_numpy(np.sort(rng.integers(0, G, T)).astype(np.int32)).cuda() if ragged else None
+    x = torch.randint(-2**15, 2**15, (T, d), dtype=torch.int16, device="cuda")
+    packed = torch.full((T * K, d), 0x7fff, dtype=torch.int16, device="cuda")
+    counts = torch.empty(G, G, dtype=torch.int32, device="cuda")
+    offsets = torch.empty(G * G + 1, dtype=torch.int64, device="cuda")
+    pos = torch.empty(T, K, dtype=torch.int32, device="cuda")
+    B.cobalt_dispatch_pack(a, src, G, x.view(torch.bfloat16), counts, offsets, pos,
+                           packed.view(torch.bfloat16), B.workspace_for(T, K, G))
+    placed = int(offsets[-1])
+    assert placed == int((a >= 0).sum())
+    # token of each row: pos names every row up to `placed` once
+    token = torch.full((T * K,), -1, dtype=torch.int64, device="cuda")
+    flat = pos.view(-1).long()
+    token[flat[flat >= 0]] = torch.arange(T, device="cuda").repeat_interleave(K)[flat >= 0]
+    assert bool((token[:placed] >= 0).all()) and bool((token[placed:] < 0).all())
+    assert torch.equal(packed[:placed], x[token[:placed]])
+    assert bool((packed[placed:] == 0x7fff).all())
