@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     if (j >= C) return;
     const int i = threadIdx.x;
     const int64_t c = (int64_t)g * (64 * C) + i;
-    if (c >= nch) return;
+    if (!kF32 && c >= nch) return;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int k = 0; k < K; ++k) {
         if (!valid[k]) continue;
@@ -93,11 +93,24 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         out[q] = pack_bf16_rne(acc[2 * q], acc[2 * q + 1]);
-    __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
-    if (kF32) {
-        float4* o = (float4*)(y32 + ((int64_t)t * nch + c) * 8);
-        o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        o[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    if (c < nch) __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
+    if constexpr (kF32) {
+        // The wave's 64 chunks are 128 16-byte pieces of y_f32; lane l stores
+        // pieces l and 64 + l, so that each store covers whole lines (two
+        // stores at its own chunk would each cover half of every line).
+        const int64_t c_wave = (int64_t)g * (64 * C) + 64 * j;
+        u32x4* o = reinterpret_cast<u32x4*>(y32) + ((int64_t)t * nch + c_wave) * 2;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int from = 32 * h + lane / 2;
+            u32x4 piece;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float lo = __shfl(acc[q], from, 64), hi = __shfl(acc[4 + q], from, 64);
+                piece[q] = __float_as_uint(lane & 1 ? hi : lo);
+            }
+            if (c_wave + from < nch) __builtin_nontemporal_store(piece, o + 64 * h + lane);
+        }
     }
 }
 
