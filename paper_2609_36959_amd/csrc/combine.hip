@@ -37,7 +37,11 @@ __device__ __forceinline__ uint32_t pack_bf16_rne(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-template <bool kF32, int C>
+// What becomes of y_f32. (The two ways of storing it are kernels of their own:
+// from the two sides of a branch the compiler makes one ordinary store.)
+enum class Sums { kNone, kStream, kKeep };
+
+template <Sums kSums, int C>
 __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     const u32x4* __restrict__ eo, const int32_t* __restrict__ pos, const float* __restrict__ gates,
     int K, int64_t nch, int64_t TK, Slices cut, u32x4* __restrict__ y, float* __restrict__ y32) {
@@ -77,7 +81,7 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     if (j >= C) return;
     const int i = threadIdx.x;
     const int64_t c = (int64_t)g * (64 * C) + i;
-    if (!kF32 && c >= nch) return;
+    if (kSums == Sums::kNone && c >= nch) return;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int k = 0; k < K; ++k) {
         if (!valid[k]) continue;
@@ -94,7 +98,7 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     for (int q = 0; q < 4; ++q)
         out[q] = pack_bf16_rne(acc[2 * q], acc[2 * q + 1]);
     if (c < nch) __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
-    if constexpr (kF32) {
+    if constexpr (kSums != Sums::kNone) {
         // The wave's 64 chunks are 128 16-byte pieces of y_f32; lane l stores
         // pieces l and 64 + l, so that each store covers whole lines (two
         // stores at its own chunk would each cover half of every line).
@@ -109,7 +113,11 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
                 const float lo = __shfl(acc[q], from, 64), hi = __shfl(acc[4 + q], from, 64);
                 piece[q] = __float_as_uint(lane & 1 ? hi : lo);
             }
-            if (c_wave + from < nch) __builtin_nontemporal_store(piece, o + 64 * h + lane);
+            if (c_wave + from >= nch) continue;
+            if constexpr (kSums == Sums::kStream)
+                __builtin_nontemporal_store(piece, o + 64 * h + lane);
+            else
+                o[64 * h + lane] = piece;
         }
     }
 }
@@ -205,9 +213,23 @@ __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
 
 }  // namespace
 
+// Whether y_f32 is stored non-temporally. Ordinary stores leave it in the
+// memory-side cache, for the kernel that reads it and for the next call that
+// writes it: T = 8192, d = 7168 take 194 us so with K = 8 and 74 with K = 2,
+// 214 and 98 non-temporally. They are the slower ones past the cache's size
+// (T = 32768, K = 8, d = 7168: 901 us against 866), with little to write (T =
+// 2048, K = 1, d = 4096: 12.8 against 11.2) and with many rows to read for
+// each that is written (T = 8192, K = 16, d = 7168: 440 against 416; T =
+// 32768, K = 8, d = 512: 67.8 against 61.5).
+static bool stream_sums(int64_t T, int K, int64_t d) {
+    const int64_t bytes = T * d * 4;
+    return bytes < (40 << 20) || bytes > (256 << 20) || K > 12 || (d <= 512 && K > 4);
+}
+
 cobalt_status launch_combine(const void* eo, const int32_t* pos, const float* gates, int64_t T,
                              int K, int64_t d, void* y, float* y32, hipStream_t s) {
     const int64_t nch = d / 8;
+    const bool stream = stream_sums(T, K, d);
     by_slices(nch, [&](auto c, const Slices& cut) {
         constexpr int C = decltype(c)::value;
         const int threads = std::max(K, C) * 64;
@@ -218,7 +240,12 @@ cobalt_status launch_combine(const void* eo, const int32_t* pos, const float* ga
                                    pos + t0 * K, gates + t0 * K, K, nch, T * K, cut,
                                    (u32x4*)y + t0 * nch, y32 ? y32 + t0 * nch * 8 : nullptr);
             };
-            y32 ? launch(fold_kernel<true, C>) : launch(fold_kernel<false, C>);
+            if (!y32)
+                launch(fold_kernel<Sums::kNone, C>);
+            else if (stream)
+                launch(fold_kernel<Sums::kStream, C>);
+            else
+                launch(fold_kernel<Sums::kKeep, C>);
         });
     });
     COBALT_LAUNCH_CHECK();

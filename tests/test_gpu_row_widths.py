@@ -1,12 +1,13 @@
 """Every call on rows at the edges of the row copies' and folds' slices (one
 chunk per lane up to 64 chunks of 16 bytes, three from 129 to 192, else two),
 with fewer and more slots than folding waves, and rows of many slices, bit for
-bit against the oracle; and packs larger than the memory-side cache, which
-move the rows in shapes of their own."""
+bit against the oracle; packs larger than the memory-side cache, which move
+the rows in shapes of their own; and fp32 sums stored in either way."""
 import numpy as np
 import pytest
 import torch
 
+import oracle
 import test_gpu_random_shapes as shapes
 from paper_2609_36959_amd import binding as B
 
@@ -62,3 +63,27 @@ def test_large_pack(K, d, ragged):
     assert bool((token[:placed] >= 0).all()) and bool((token[placed:] < 0).all())
     assert torch.equal(packed[:placed], x[token[:placed]])
     assert bool((packed[placed:] == 0x7fff).all())
+
+
+# y_f32 of 40 to 256 MiB is kept in the cache (42 MB, a row of 129 chunks; 41
+# MB, a row of 1025; 42 and 268 MB), but not for short rows of many slots or
+# many slots at all; more is streamed
+@pytest.mark.parametrize("T,K,d", [(10304, 2, 1032), (1300, 4, 8200), (20480, 4, 512),
+                                   (32768, 1, 2048), (20480, 8, 512), (5200, 12, 2048),
+                                   (5200, 13, 2048), (32800, 1, 2048)])
+def test_fp32_sums(T, K, d):
+    print(f"fp32 sums T={T} K={K} d={d}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + K + d)
+    eo = torch.randn(T * K, d, device="cuda", generator=g).bfloat16()
+    pos = torch.randperm(T * K, device="cuda", generator=g).int().view(T, K)
+    gates = torch.rand(T, K, device="cuda", generator=g)
+    y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y32 = torch.full((T, d), float("nan"), device="cuda")
+    B.cobalt_combine(eo, pos, gates, y, y32)
+    assert torch.equal(y, y32.bfloat16())
+    t = torch.cat([torch.arange(3), torch.randint(0, T, (40,)), torch.arange(T - 3, T)]).cuda()
+    rows = eo[pos[t].long().view(-1)].view(torch.int16).cpu().numpy().view(np.uint16)
+    ref, ref32 = oracle.combine(rows, np.arange(len(t) * K, dtype=np.int32).reshape(-1, K),
+                                gates[t].cpu().numpy())
+    assert np.array_equal(y[t].view(torch.int16).cpu().numpy().view(np.uint16), ref)
+    assert np.array_equal(y32[t].cpu().numpy().view(np.uint32), ref32.view(np.uint32))
