@@ -13,6 +13,9 @@
 // chunks of all K rows. Twice the folding waves, 8 bytes per thread, took 3 %
 // longer, and half as many, two chunks per lane, hold the stage longer still.
 //
+// direct_kernel (the widest rows, where direct_fold says so): one wave per
+// (token, 1 KiB slice) loads the chunks of all K rows itself.
+//
 // The node-level combine (the reverse of the node-deduplicated dispatch)
 // follows: node_fold_kernel sums each node's slots into a bf16 partial row
 // and the token's partial rows, in node order, into y.
@@ -122,6 +125,61 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     }
 }
 
+// Each wave takes one (token, slice of 64 chunks) and loads the chunks of all
+// K rows, issuing every load before its single store so that no load waits
+// behind a store. KM: slots held in registers, at least K (kFull: exactly K).
+constexpr int kDirectWaves = 16;
+
+template <bool kF32, int KM, bool kFull>
+__global__ __launch_bounds__(kDirectWaves * 64) void direct_kernel(
+    const u32x4* __restrict__ eo, const int32_t* __restrict__ pos, const float* __restrict__ gates,
+    int64_t T, int Kr, int64_t nch, int64_t TK, u32x4* __restrict__ y, float* __restrict__ y32) {
+    const int K = kFull ? KM : Kr;
+    const int64_t slices = (nch + 63) / 64;
+    // wave-uniform item index, so pos and gates come in through scalar loads
+    const int64_t item = (int64_t)blockIdx.x * kDirectWaves +
+                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (item >= T * slices) return;
+    const int64_t t = item / slices;
+    const int64_t c = (item - t * slices) * 64 + (threadIdx.x & 63);
+    int p[KM];
+    float g[KM];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+        p[j] = j < K ? pos[t * K + j] : -1;
+        g[j] = j < K ? gates[t * K + j] : 0.f;
+    }
+    u32x4 v[KM];
+    bool ok[KM];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+        ok[j] = p[j] >= 0 && p[j] < TK && c < nch;
+        if (ok[j]) v[j] = __builtin_nontemporal_load(eo + (int64_t)p[j] * nch + c);
+    }
+    if (c >= nch) return;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+        if (!ok[j]) continue;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            acc[2 * q] = __builtin_fmaf(g[j], __uint_as_float(v[j][q] << 16), acc[2 * q]);
+            acc[2 * q + 1] =
+                __builtin_fmaf(g[j], __uint_as_float(v[j][q] & 0xffff0000u), acc[2 * q + 1]);
+        }
+    }
+    u32x4 out;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        out[q] = pack_bf16_rne(acc[2 * q], acc[2 * q + 1]);
+    __builtin_nontemporal_store(out, y + t * nch + c);
+    if constexpr (kF32) {
+        float4* o = reinterpret_cast<float4*>(y32 + (t * nch + c) * 8);
+        o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        o[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    }
+}
+
 // Node-level combine: one workgroup per (token, 2 KiB column slice), one wave
 // per slot j (at least two waves). Wave j loads its row's slice like
 // fold_kernel and records its gate and its rank's node; after a barrier two
@@ -226,9 +284,39 @@ static bool stream_sums(int64_t T, int K, int64_t d) {
     return bytes < (40 << 20) || bytes > (256 << 20) || K > 12 || (d <= 512 && K > 4);
 }
 
+// Whether direct_kernel folds the rows: only rows of more than 2048 chunks (d >
+// 16384) in enough waves to fill the chip, where K > 12 makes fold_kernel's
+// workgroups so large that two of them fill a CU's waves (K = 16, d = 20480: T
+// = 64 8.3 us against 11.0, T = 1024 116 against 141; T = 16 6.2 against 4.8),
+// or where all its waves are in flight at once (T = 64, d = 32768: K = 8 5.3
+// us against 7.7, K = 12 8.0 against 10.2).
+static bool direct_fold(int64_t T, int K, int64_t nch) {
+    const int64_t waves = T * ((nch + 63) / 64);
+    return nch > 2048 && K >= 8 && waves > 2048 && (K > 12 || waves <= 4096);
+}
+
 cobalt_status launch_combine(const void* eo, const int32_t* pos, const float* gates, int64_t T,
                              int K, int64_t d, void* y, float* y32, hipStream_t s) {
     const int64_t nch = d / 8;
+    if (direct_fold(T, K, nch)) {
+        const int64_t slices = (nch + 63) / 64;  // one wave each
+        for_token_ranges(T, slices * 64, [&](int64_t t0, int64_t n) {
+            const unsigned blocks = (unsigned)((n * slices + kDirectWaves - 1) / kDirectWaves);
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kDirectWaves * 64), 0, s,
+                                   (const u32x4*)eo, pos + t0 * K, gates + t0 * K, n, K, nch,
+                                   T * K, (u32x4*)y + t0 * nch,
+                                   y32 ? y32 + t0 * nch * 8 : nullptr);
+            };
+            if (K == 8)
+                y32 ? launch(direct_kernel<true, 8, true>) : launch(direct_kernel<false, 8, true>);
+            else
+                y32 ? launch(direct_kernel<true, kMaxK, false>)
+                    : launch(direct_kernel<false, kMaxK, false>);
+        });
+        COBALT_LAUNCH_CHECK();
+        return COBALT_OK;
+    }
     const bool stream = stream_sums(T, K, d);
     by_slices(nch, [&](auto c, const Slices& cut) {
         constexpr int C = decltype(c)::value;

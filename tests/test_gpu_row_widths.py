@@ -31,6 +31,18 @@ def test_row_width(nch, K, N):
     shapes.test_random_shape(N, 2, 18 if N != 2 else 20, 18, K, 37, 8 * nch, "ragged", nch + K)
 
 
+# rows of more than 2048 chunks whose combine needs no workgroup per token:
+# eight slots and others, few waves and (K > 12) many, a short last slice, and
+# the same split into many launches
+@pytest.mark.parametrize("T,nch", [(70, 2049), (64, 2113), (64, 4096), (130, 2176)])
+@pytest.mark.parametrize("K", [8, 9, 13, 16])
+@pytest.mark.parametrize("limit", [None, 1 << 16])
+def test_wide_row(T, nch, K, limit, monkeypatch):
+    if limit:
+        monkeypatch.setenv("COBALT_MAX_LAUNCH_ITEMS", str(limit))
+    shapes.test_random_shape(3, 2, 18, 18, K, T, 8 * nch, "ragged", nch + K)
+
+
 # outputs of more than 256 MiB: every K with 1 KiB slices (two rows per wave
 # from K = 3), rows of an odd number of KiB, of no power of two, of no whole
 # KiB; equal blocks of sources with buckets of 16 MiB, and sources given
