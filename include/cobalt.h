@@ -11,7 +11,10 @@
  *  - Pointers are DEVICE pointers unless the name starts with host_.
  *  - Arrays are dense, row-major, in the element type of the declaration;
  *    bf16 rows are raw 16-bit patterns, 16-byte aligned.
- *  - The caller owns every buffer. The four path calls (cobalt_coact_stats,
+ *  - The caller owns every buffer. Buffers of one call do not overlap, but an
+ *    output may take the place of an input that it matches element by element
+ *    (assigned_rank over topk_idx, pos over assigned_rank, node_pos over
+ *    assigned_rank where N = K). The four path calls (cobalt_coact_stats,
  *    cobalt_assign, cobalt_dispatch_pack, cobalt_combine) allocate nothing,
  *    enqueue their kernels on `stream` (a hipStream_t; NULL = the default
  *    stream of the current device) and return without synchronising.

@@ -157,6 +157,13 @@ void by_slices(int64_t nch, F&& f) {
         f(std::integral_constant<int, 3>(), cut);
 }
 
+// Whether na bytes at a and nb bytes at b share any. A caller may give an
+// output the memory of an input that the call has no more use for; kernels
+// that write the one while others still read the other ask first.
+inline bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
+    return a && b && (const char*)a < (const char*)b + nb && (const char*)b < (const char*)a + na;
+}
+
 struct DeviceLayout {
     int device;
     int32_t N, g, G, E, S;

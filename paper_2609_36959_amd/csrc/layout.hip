@@ -955,6 +955,14 @@ static int64_t small_pairs(bool src, int G) {
     return std::min<int64_t>(kSmallPairsAny, kSmallPairs + 2304 * (int64_t)G);
 }
 
+// Whole-call workgroups read all ranks and sources while others write rows, so
+// they are not for a call that puts the rows in their place (the other schemes
+// read a tile before they write its rows).
+static bool in_place(const int32_t* rows, int64_t n, const int32_t* assigned, int64_t pairs,
+                     const int32_t* src, int64_t T) {
+    return overlap(rows, 4 * n, assigned, 4 * pairs) || overlap(rows, 4 * n, src, 4 * T);
+}
+
 // Clears counts[R][C] in a kernel: a recorded memset node is no part of a
 // captured call.
 static void launch_clear(int32_t* counts, int n, hipStream_t s) {
@@ -978,7 +986,8 @@ cobalt_status launch_layout(const int32_t* assigned, const int32_t* src, int64_t
     if (T == 0) {
         launch_clear(counts, G * G, s);
         launch_scan(counts, G, G, offsets, base, s);
-    } else if (G <= kSmallG && TK <= small_pairs(src != nullptr, G)) {
+    } else if (G <= kSmallG && TK <= small_pairs(src != nullptr, G) &&
+               !in_place(pos, TK, assigned, TK, src, T)) {
         const unsigned blocks = (unsigned)((TK + kThreads - 1) / kThreads);
         hipLaunchKernelGGL(small_layout_kernel, dim3(blocks), dim3(kThreads), 0, s, assigned, src,
                            (int)TK, G, divide_by(K), divide_by(src ? 1 : TK / G), counts, offsets,
@@ -1027,7 +1036,8 @@ cobalt_status launch_node_layout(const int32_t* assigned, const int32_t* src, in
     }
     by_row(K, assigned, [&](auto km, auto vec) {
         constexpr int KM = decltype(km)::value, V = decltype(vec)::value;
-        if (table && T <= (src ? kSmallTokensAny : kSmallTokens)) {
+        if (table && T <= (src ? kSmallTokensAny : kSmallTokens) &&
+            !in_place(node_pos, T * N, assigned, T * K, src, T)) {
             const unsigned blocks = (unsigned)((T + kThreads - 1) / kThreads);
             auto launch = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, s, assigned, src,
