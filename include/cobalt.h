@@ -14,7 +14,8 @@
  *  - The caller owns every buffer. Buffers of one call do not overlap, but an
  *    output may take the place of an input that it matches element by element
  *    (assigned_rank over topk_idx, pos over assigned_rank, node_pos over
- *    assigned_rank where N = K). The four path calls (cobalt_coact_stats,
+ *    assigned_rank where N = K), and the y of cobalt_node_combine may lie in
+ *    expert_out. The four path calls (cobalt_coact_stats,
  *    cobalt_assign, cobalt_dispatch_pack, cobalt_combine) allocate nothing,
  *    enqueue their kernels on `stream` (a hipStream_t; NULL = the default
  *    stream of the current device) and return without synchronising.

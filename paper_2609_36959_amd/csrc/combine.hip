@@ -191,7 +191,8 @@ __global__ __launch_bounds__(kDirectWaves * 64) void direct_kernel(
 // T=131072, K=8, N=8, d=7168 workload (3.93 + 1.67), now 4.35 ms (5.8 TB/s of
 // mixed reads and writes). One wave per node row, with the partials summed
 // through LDS after a second barrier, took 4.46 ms; plain instead of
-// non-temporal stores of the partial rows 4.42 ms.
+// non-temporal stores of the partial rows 4.42 ms. Without y the partial rows
+// are all it writes, and node_sum_kernel follows.
 template <int C>
 __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
     const u32x4* __restrict__ eo, const int32_t* __restrict__ pos,
@@ -261,12 +262,43 @@ __global__ __launch_bounds__(kMaxK * 64) void node_fold_kernel(
         const int q = __builtin_amdgcn_readlane(row, n);
         if (c < nch) __builtin_nontemporal_store(part, partial + (int64_t)q * nch + c);
     }
-    if (c >= nch) return;
+    if (!y || c >= nch) return;
     u32x4 out;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         out[e] = pack_bf16_rne(sum[2 * e], sum[2 * e + 1]);
     __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
+}
+
+// y from the partial rows, for a y in the memory of the expert rows (or of
+// another input), which node_fold_kernel reads until its last workgroup: one
+// wave per (token, slice of 64 chunks).
+__global__ __launch_bounds__(kDirectWaves * 64) void node_sum_kernel(
+    const u32x4* __restrict__ partial, const int32_t* __restrict__ node_pos, int64_t T, int N,
+    int64_t nch, int64_t node_rows, u32x4* __restrict__ y) {
+    const int64_t slices = (nch + 63) / 64;
+    const int64_t item = (int64_t)blockIdx.x * kDirectWaves +
+                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (item >= T * slices) return;
+    const int64_t t = item / slices;
+    const int64_t c = (item - t * slices) * 64 + (threadIdx.x & 63);
+    float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < N; ++n) {
+        const int q = node_pos[t * N + n];
+        if (q < 0 || q >= node_rows || c >= nch) continue;
+        const u32x4 v = __builtin_nontemporal_load(partial + (int64_t)q * nch + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sum[2 * e] += __uint_as_float(v[e] << 16);
+            sum[2 * e + 1] += __uint_as_float(v[e] & 0xffff0000u);
+        }
+    }
+    if (c >= nch) return;
+    u32x4 out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        out[e] = pack_bf16_rne(sum[2 * e], sum[2 * e + 1]);
+    __builtin_nontemporal_store(out, y + t * nch + c);
 }
 
 }  // namespace
@@ -346,6 +378,10 @@ cobalt_status launch_node_combine(const void* eo, const int32_t* pos, const int3
                                   hipStream_t s) {
     const int64_t nch = d / 8;
     const int64_t node_rows = T * std::min(K, N);
+    const bool apart = overlap(y, T * d * 2, eo, T * K * d * 2) ||
+                       overlap(y, T * d * 2, pos, T * K * 4) ||
+                       overlap(y, T * d * 2, assigned, T * K * 4) ||
+                       overlap(y, T * d * 2, gates, T * K * 4);
     by_slices(nch, [&](auto c, const Slices& cut) {
         constexpr int C = decltype(c)::value;
         const int threads = std::max(K, C) * 64;
@@ -354,9 +390,18 @@ cobalt_status launch_node_combine(const void* eo, const int32_t* pos, const int3
                                (size_t)K * 64 * C * sizeof(u32x4), s, (const u32x4*)eo,
                                pos + t0 * K, assigned + t0 * K, gates + t0 * K, node_pos + t0 * N,
                                K, N, gpn, nch, T * K, node_rows, cut, (u32x4*)partial,
-                               (u32x4*)y + t0 * nch);
+                               apart ? nullptr : (u32x4*)y + t0 * nch);
         });
     });
+    if (apart) {
+        const int64_t slices = (nch + 63) / 64;  // one wave each
+        for_token_ranges(T, slices * 64, [&](int64_t t0, int64_t n) {
+            const unsigned blocks = (unsigned)((n * slices + kDirectWaves - 1) / kDirectWaves);
+            hipLaunchKernelGGL(node_sum_kernel, dim3(blocks), dim3(kDirectWaves * 64), 0, s,
+                               (const u32x4*)partial, node_pos + t0 * N, n, N, nch, node_rows,
+                               (u32x4*)y + t0 * nch);
+        });
+    }
     COBALT_LAUNCH_CHECK();
     return COBALT_OK;
 }
