@@ -91,16 +91,16 @@ def _call(name: str, *args) -> None:
 
 # torch.cuda.current_stream() builds a Stream object, 2.8 us of a call that
 # takes 4 us with its launch; the raw handle of the same stream takes 0.1 us.
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_device = torch._C._cuda_getDevice
+# The two functions for it are torch's own, not part of its interface: without
+# them the handle comes from the Stream object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is not None:
-        return stream.cuda_stream
-    if not torch.cuda.is_initialized():
-        return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(_device())
+    if stream is None and _raw_stream and _device and torch.cuda.is_initialized():
+        return _raw_stream(_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _dev(t: Optional[torch.Tensor], name: str, dtypes, shape=None) -> Optional[int]:
