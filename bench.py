@@ -29,10 +29,12 @@ sys.path.insert(0, ROOT)
 HBM_PEAK = 8.0e12  # MI355X HBM3E, bytes/s
 METRIC = "routed tokens/sec (stats+assign+pack+combine), % of HBM peak, 1 MI355X"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_{call}_{workload}.txt")
-KERNEL_SOURCES = {"cobalt_dispatch_pack": ("dispatch.hip", "layout.hip"),
-                  "cobalt_combine": ("combine.hip",),
-                  "cobalt_node_dispatch_pack": ("dispatch.hip", "layout.hip"),
-                  "cobalt_node_combine": ("combine.hip",)}
+# the files that a call's kernels are built from, headers included: measured
+# traffic holds for these as they were
+KERNEL_SOURCES = {"cobalt_dispatch_pack": ("dispatch.hip", "layout.hip", "internal.hpp"),
+                  "cobalt_combine": ("combine.hip", "internal.hpp"),
+                  "cobalt_node_dispatch_pack": ("dispatch.hip", "layout.hip", "internal.hpp"),
+                  "cobalt_node_combine": ("combine.hip", "internal.hpp")}
 
 
 def parse():

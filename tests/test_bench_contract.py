@@ -1,7 +1,9 @@
 """bench.py's output contract: one JSON line with the required fields, and a
 clear refusal of more than one GPU (checked without touching a GPU)."""
+import importlib.util
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -16,6 +18,21 @@ def test_more_than_one_gpu_is_refused():
     assert r.returncode == 2
     assert "one GPU only" in r.stderr
     assert r.stdout == ""
+
+
+def test_traffic_digests_cover_the_headers():
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    csrc = os.path.join(ROOT, "paper_2609_36959_amd", "csrc")
+    for call, files in bench.KERNEL_SOURCES.items():
+        for name in files:
+            with open(os.path.join(csrc, name)) as f:
+                included = re.findall(r'^#include "(.*)"', f.read(), re.M)
+            for h in included:
+                # the C header holds no kernel code
+                assert h in files or h == "cobalt.h", f"{call}: {name} includes {h}"
+        assert len(bench.source_digest(call)) == 16
 
 
 @pytest.mark.gpu
