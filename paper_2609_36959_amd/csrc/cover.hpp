@@ -34,8 +34,14 @@ __host__ __device__ inline u16x2 zero_halves(u16x2 v) {
 //  - a node no unmet mask can use is in no smallest set;
 //  - with one node to go, the nodes common to all unmet masks decide at once.
 // Decisions go down in node order, so the last node left out is the lowest
-// bit of X. A dead end takes that node instead and forgets every lower
-// decision; S and E are derived again by the passes that follow.
+// bit of X: on a branch masks only get met and nodes only drop out, so the
+// highest usable node only falls. A dead end takes that last node instead and
+// forgets every lower decision, and S and E with them, since they may follow
+// from what is undone. A decision waits until a pass derives nothing more, so
+// what S and E held before the undone decision has followed again from the
+// decisions that stand, and one mask is met besides: the next decision is
+// below the node again (so it was on 340 million decisions for 300 million
+// random sets of masks, 8 and 16 of them over up to 15 nodes).
 //
 // A pass is straight-line code on pairs of 16-bit masks, about 100
 // instructions for eight masks, and the wave runs as many passes as its

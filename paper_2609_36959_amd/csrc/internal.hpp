@@ -90,7 +90,8 @@ __device__ __forceinline__ void store_row(int32_t* row, int K, const int (&v)[KM
 }
 
 // Calls f(KM, VEC) for rows of K ints at `p`: KM slots in registers, VEC ints
-// per access.
+// per access. Without 8-byte accesses K = 2, 6 and 10 take 1.8 % longer in the
+// node layouts (144 sizes) and 2.3 % in the statistics (27).
 template <typename F>
 void by_row(int K, const void* p, F&& f) {
     auto vec = [&](auto km) {

@@ -20,7 +20,11 @@
 //     kSmallTable). The counts per bucket come from atomic adds on a window
 //     of sources per tile, the earlier tiles of a destination from the
 //     tiles' counts; each workgroup turns the counts into first rows itself.
-//     65536 pairs on 4 x 8: 14.8 | 13.4 (16.4 | 18.9).
+//     65536 pairs on 4 x 8: 14.8 | 13.4 (16.4 | 18.9). With the scan in
+//     between, 131072 tokens, K = 8: 8 x 16 ranks 41.5 | 20.0 (43.8 | 34.1),
+//     16 x 16 175 | 30.2 (171 | 48.6), 16 x 32 559 | 44.6 (571 | 59.8); the
+//     scan's workgroup takes most of it (equal blocks, which need none: 10.0 |
+//     10.6, 10.8 | 15.1, 16.1 | 16.5).
 //   whole-call workgroups (small calls; one kernel). Every workgroup counts
 //     all items of the call in its LDS, which costs less than another launch
 //     up to a limit: 2048 pairs on 4 x 8 take 5.5 | 5.9 (13.2 | 15.3). Equal
@@ -1027,6 +1031,7 @@ cobalt_status launch_node_layout(const int32_t* assigned, const int32_t* src, in
     const int G = N * g;
     int32_t* base = (int32_t*)ws;
     const bool table = G * N <= kSmallTable;
+    // whole rows of node_pos per store (without: 6 % longer over 192 sizes)
     const bool nv = N % 4 == 0 && ((uintptr_t)node_pos & 15u) == 0;
     if (T == 0) {
         launch_clear(counts, G * N, s);

@@ -87,7 +87,6 @@ struct Plan {
     int lgb;                // log2 of the number of bands
     bool u16;               // partial bins stored as uint16
     int64_t tok_per_chunk;
-    int64_t words;          // E(E-1)/2
     int64_t band_stride;    // bins of the largest band (band 0), rounded up to 8
     int32_t cnt_off;        // LDS word of the band's expert counts (then its diagonal)
     size_t lds_bytes;
@@ -116,7 +115,6 @@ int64_t hist_words(int E, int nb) { return round_up(std::max(band_words(E, nb, 0
 int64_t cnt_words(int E, int nb) { return round_up((E + nb - 1) / nb, 4); }
 
 bool make_plan(int64_t T, int64_t K, int E, int lds_bytes, Plan* p) {
-    p->words = (int64_t)E * (E - 1) / 2;
     const int64_t lds_words = lds_bytes / 4;
     auto fits = [&](int l) { return hist_words(E, 1 << l) + 2 * cnt_words(E, 1 << l) <= lds_words; };
     // fewest bands whose largest band and counts fit the LDS
@@ -263,9 +261,10 @@ __device__ __forceinline__ void count_token(int (&e)[KM], int K, int E, int lgb,
 }
 
 // KM: ids held in registers, at least K (kFull: exactly K, so that no slot is
-// tested for); VEC: ids per load (load_row). Ids outside [0, E) sort last as INT_MAX and count nowhere. U16: partial bins
-// written as uint16. A thread takes two tokens per iteration and issues both
-// loads before either is counted.
+// tested for); VEC: ids per load (load_row). Ids outside [0, E) sort last as
+// INT_MAX and count nowhere. U16: partial bins written as uint16. A thread
+// takes two tokens per iteration and issues both loads before either is
+// counted.
 template <int KM, int VEC, bool kFull, bool U16>
 __global__ __launch_bounds__(kCountThreads) void coact_count_kernel(
     const int32_t* __restrict__ topk, int64_t T, int Kr, int E, int lgb, int nchunks,

@@ -1,7 +1,6 @@
 """The cover search of the assignment kernel (csrc/cover.hpp), built for the
 host, against its definition: the first set of nodes in the order (size,
 value) that meets every mask, found by trying all sets in that order."""
-import os
 import subprocess
 
 import numpy as np

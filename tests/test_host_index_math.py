@@ -4,7 +4,6 @@ to 4096 and at the ends of the index range, and the small division for every
 dividend below 2^17 at divisors over its range."""
 import subprocess
 
-
 from paper_2609_36959_amd import build as hip_build
 
 DRIVER = r"""
