@@ -40,9 +40,10 @@ __device__ __forceinline__ uint32_t pack_bf16_rne(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// What becomes of y_f32. (The two ways of storing it are kernels of their own:
-// from the two sides of a branch the compiler makes one ordinary store.)
-enum class Sums { kNone, kStream, kKeep };
+// How y_f32 is stored (store_sums chooses): in whole lines, non-temporally or
+// not, or by each thread at its own chunk. (They are kernels of their own: from
+// the two sides of a branch the compiler makes one ordinary store.)
+enum class Sums { kNone, kStream, kKeep, kDirect };
 
 template <Sums kSums, int C>
 __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     if (j >= C) return;
     const int i = threadIdx.x;
     const int64_t c = (int64_t)g * (64 * C) + i;
-    if (kSums == Sums::kNone && c >= nch) return;
+    if ((kSums == Sums::kNone || kSums == Sums::kDirect) && c >= nch) return;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int k = 0; k < K; ++k) {
         if (!valid[k]) continue;
@@ -101,7 +102,11 @@ __global__ __launch_bounds__(kMaxK * 64) void fold_kernel(
     for (int q = 0; q < 4; ++q)
         out[q] = pack_bf16_rne(acc[2 * q], acc[2 * q + 1]);
     if (c < nch) __builtin_nontemporal_store(out, y + (int64_t)t * nch + c);
-    if constexpr (kSums != Sums::kNone) {
+    if constexpr (kSums == Sums::kDirect) {
+        float4* o = reinterpret_cast<float4*>(y32 + ((int64_t)t * nch + c) * 8);
+        o[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        o[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    } else if constexpr (kSums != Sums::kNone) {
         // The wave's 64 chunks are 128 16-byte pieces of y_f32; lane l stores
         // pieces l and 64 + l, so that each store covers whole lines (two
         // stores at its own chunk would each cover half of every line).
@@ -303,17 +308,21 @@ __global__ __launch_bounds__(kDirectWaves * 64) void node_sum_kernel(
 
 }  // namespace
 
-// Whether y_f32 is stored non-temporally. Ordinary stores leave it in the
-// memory-side cache, for the kernel that reads it and for the next call that
-// writes it: T = 8192, d = 7168 take 194 us so with K = 8 and 74 with K = 2,
-// 214 and 98 non-temporally. They are the slower ones past the cache's size
-// (T = 32768, K = 8, d = 7168: 901 us against 866), with little to write (T =
-// 2048, K = 1, d = 4096: 12.8 against 11.2) and with many rows to read for
-// each that is written (T = 8192, K = 16, d = 7168: 440 against 416; T =
-// 32768, K = 8, d = 512: 67.8 against 61.5).
-static bool stream_sums(int64_t T, int K, int64_t d) {
+// Below 2 MiB the time is latency, and the exchange between lanes that makes
+// whole lines costs what it saves elsewhere (T = 290, K = 8, d = 1032 4.1 us
+// without it, 4.8 with). Non-temporal stores are faster up to where the
+// memory-side cache's reuse sets in (T = 2180, K = 3, d = 1032: 5.9 us against
+// 6.9), past its size (T = 32768, K = 8, d = 7168: 866 against 901) and with
+// many rows to read for each that is written (T = 8192, K = 16, d = 7168: 416
+// against 440; T = 32768, K = 8, d = 512: 61.5 against 67.8). In between,
+// ordinary stores leave the sums in that cache for the kernel that reads them
+// and for the next call that writes them: T = 8192, d = 7168 take 194 us so
+// with K = 8 and 74 with K = 2, 214 and 98 non-temporally.
+static Sums store_sums(int64_t T, int K, int64_t d) {
     const int64_t bytes = T * d * 4;
-    return bytes < (40 << 20) || bytes > (256 << 20) || K > 12 || (d <= 512 && K > 4);
+    if (bytes < (2 << 20)) return Sums::kDirect;
+    const bool cached = bytes >= (40 << 20) && bytes <= (256 << 20);
+    return cached && K <= 12 && (d > 512 || K <= 4) ? Sums::kKeep : Sums::kStream;
 }
 
 // Whether direct_kernel folds the rows: only rows of more than 2048 chunks (d >
@@ -349,7 +358,7 @@ cobalt_status launch_combine(const void* eo, const int32_t* pos, const float* ga
         COBALT_LAUNCH_CHECK();
         return COBALT_OK;
     }
-    const bool stream = stream_sums(T, K, d);
+    const Sums sums = y32 ? store_sums(T, K, d) : Sums::kNone;
     by_slices(nch, [&](auto c, const Slices& cut) {
         constexpr int C = decltype(c)::value;
         const int threads = std::max(K, C) * 64;
@@ -360,12 +369,14 @@ cobalt_status launch_combine(const void* eo, const int32_t* pos, const float* ga
                                    pos + t0 * K, gates + t0 * K, K, nch, T * K, cut,
                                    (u32x4*)y + t0 * nch, y32 ? y32 + t0 * nch * 8 : nullptr);
             };
-            if (!y32)
+            if (sums == Sums::kNone)
                 launch(fold_kernel<Sums::kNone, C>);
-            else if (stream)
+            else if (sums == Sums::kStream)
                 launch(fold_kernel<Sums::kStream, C>);
-            else
+            else if (sums == Sums::kKeep)
                 launch(fold_kernel<Sums::kKeep, C>);
+            else
+                launch(fold_kernel<Sums::kDirect, C>);
         });
     });
     COBALT_LAUNCH_CHECK();

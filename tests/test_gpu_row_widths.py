@@ -77,10 +77,11 @@ def test_large_pack(K, d, ragged):
     assert bool((packed[placed:] == 0x7fff).all())
 
 
-# y_f32 of 40 to 256 MiB is kept in the cache (42 MB, a row of 129 chunks; 41
-# MB, a row of 1025; 42 and 268 MB), but not for short rows of many slots or
-# many slots at all; more is streamed
-@pytest.mark.parametrize("T,K,d", [(10304, 2, 1032), (1300, 4, 8200), (20480, 4, 512),
+# y_f32 below 2 MiB (5 rows of a chunk; 1.98 MB, 2.03 MB); of 40 to 256 MiB (42
+# MB, a row of 129 chunks; 43 MB, a row of 1025; 42 and 268 MB), but not for
+# short rows of many slots or many slots at all; others
+@pytest.mark.parametrize("T,K,d", [(5, 12, 8), (510, 6, 1016), (517, 6, 1016), (3, 16, 1544),
+                                   (10304, 2, 1032), (1300, 4, 8200), (20480, 4, 512),
                                    (32768, 1, 2048), (20480, 8, 512), (5200, 12, 2048),
                                    (5200, 13, 2048), (32800, 1, 2048)])
 def test_fp32_sums(T, K, d):
