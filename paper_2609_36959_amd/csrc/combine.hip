@@ -359,7 +359,10 @@ cobalt_status launch_combine(const void* eo, const int32_t* pos, const float* ga
         return COBALT_OK;
     }
     const Sums sums = y32 ? store_sums(T, K, d) : Sums::kNone;
-    by_slices(nch, [&](auto c, const Slices& cut) {
+    // with one or two slots a fold of three chunks per lane has waves that load
+    // nothing: T = 16384, K = 1, d = 1536 24.1 us, with two chunks 20.1 (but with
+    // y_f32 T = 65536, K = 1, d = 1280 128.8 against 147.3)
+    by_slices(nch, K < 3 && !y32 ? 2 : 3, [&](auto c, const Slices& cut) {
         constexpr int C = decltype(c)::value;
         const int threads = std::max(K, C) * 64;
         for_token_ranges(T, (int64_t)cut.slices * threads, [&](int64_t t0, int64_t n) {
@@ -393,7 +396,7 @@ cobalt_status launch_node_combine(const void* eo, const int32_t* pos, const int3
                        overlap(y, T * d * 2, pos, T * K * 4) ||
                        overlap(y, T * d * 2, assigned, T * K * 4) ||
                        overlap(y, T * d * 2, gates, T * K * 4);
-    by_slices(nch, [&](auto c, const Slices& cut) {
+    by_slices(nch, 3, [&](auto c, const Slices& cut) {
         constexpr int C = decltype(c)::value;
         const int threads = std::max(K, C) * 64;
         for_token_ranges(T, (int64_t)cut.slices * threads, [&](int64_t t0, int64_t n) {

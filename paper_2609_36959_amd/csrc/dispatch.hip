@@ -196,7 +196,7 @@ cobalt_status launch_node_dispatch(const int32_t* assigned, const int32_t* src, 
         return st;
     if (T == 0 || !x) return COBALT_OK;
     const int64_t nch = d / 8, bound = T * std::min(K, N);
-    by_slices(nch, [&](auto c, const Slices& cut) {
+    by_slices(nch, 3, [&](auto c, const Slices& cut) {
         constexpr int C = decltype(c)::value;
         const int threads = kNodeScatterWaves * 64;
         for_token_ranges(T, (int64_t)cut.slices * threads, [&](int64_t t0, int64_t n) {

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <type_traits>
@@ -145,10 +146,11 @@ inline int chunks_per_lane(int64_t nch) {
     return nch <= 64 ? 1 : nch > 128 && nch <= 192 ? 3 : 2;
 }
 
-// Calls f(C, cut) with the row's chunks per lane C and its slices.
+// Calls f(C, cut) with the row's chunks per lane C, at most `most`, and its
+// slices.
 template <typename F>
-void by_slices(int64_t nch, F&& f) {
-    const int c = chunks_per_lane(nch);
+void by_slices(int64_t nch, int most, F&& f) {
+    const int c = std::min(chunks_per_lane(nch), most);
     const Slices cut = cut_row(nch, c);
     if (c == 1)
         f(std::integral_constant<int, 1>(), cut);
